@@ -195,7 +195,8 @@ typedef struct ipcs_run_s* ipcs_run;
  * factor of about 1e7 of its terms' magnitudes on fine meshes, so FP32 values
  * would leave it dominated by their rounding. The pressure Poisson solve is an FP64
  * iterative refinement on the FP64 Kp, to ||r - Kp dP|| <= tol_ir ||r||,
- * around Jacobi-CG on Kp rounded to FP32. Each pass asks the inner CG for the
+ * around Jacobi-CG on Kp rounded to FP32 (multigrid CG: on the FP64 Kp, the
+ * preconditioner's values in FP32). Each pass asks the inner CG for the
  * reduction still needed, but not below half of the reduction the previous
  * pass achieved, nor below tol_p; an inner breakdown (the rounded singular
  * Kp can be marginally indefinite) ends that pass at its last iterate and
@@ -269,11 +270,15 @@ typedef struct {
                          * polls near its expected end (fewer when one
                          * iteration costs more than a poll)                */
   int32_t callbacks;    /* 1: reserve staging for host-callback forcing        */
-  int32_t poisson_part_rows; /* pressure Poisson CG form: 0 (default) one kernel
+  int32_t poisson_part_rows; /* pressure Poisson CG form: 0 (default, with
+                           * poisson_s 0) CG with a multigrid preconditioner
+                           * above 2560 pressure rows after a momentum solve
+                           * of at most 40 iterations, else (and where it
+                           * fails) Jacobi-CG in one kernel
                            * per iteration on a row partition of Kp into parts
                            * of at most 384 rows, falling back to two kernels
                            * where a part's halo does not fit in LDS; 64..2048
-                           * the same with that part size (IPCS_E_CAPACITY if
+                           * the Jacobi-CG with that part size (IPCS_E_CAPACITY if
                            * it does not fit); -1 two kernels per iteration
                            * (SpMV, then the vector update)                  */
   int32_t scheme;       /* IPCS_SCHEME_IPCS (default) or IPCS_SCHEME_CHORIN    */

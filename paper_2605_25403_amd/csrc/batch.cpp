@@ -72,21 +72,24 @@ KSet& set_of(Run& r, int which) {
 // Plan of one shared launch set: its runs, block maps and the offsets of its
 // descriptors in the solve's descriptor space.
 struct Plan {
-  bool fused = false;
+  bool fused = false, mg = false;
   std::vector<Run*> rs;
   std::vector<int2> bm, bv, bf;
+  size_t o_mgroups = 0;
   size_t o_groups = 0, o_bm = 0, o_bv = 0, o_poll = 0, o_fgroups = 0, o_bf = 0, o_compact = 0;
 };
 
 // Plans the shared sets for system set `which` (0 momentum, 1 Poisson,
 // 2 correction) of the given runs; returns the bytes their descriptors take.
 size_t plan_shared(const std::vector<Run*>& runs, int which, std::vector<Plan>& plans) {
-  // fused Poisson sets: (1, iterations per launch, rows per thread, value type);
-  // others: (0, ns, ept_m, value type)
+  // multigrid Poisson sets: (2, rows per thread, preconditioner's and matrix's
+  // value types); fused Poisson sets: (1, iterations per launch, rows per
+  // thread, value type); others: (0, ns, ept_m, value type)
   std::map<std::tuple<int, int, int, int>, std::vector<Run*>> cls;
   for (Run* r : runs) {
     const KSet& K = set_of(*r, which);
-    if (K.fused) cls[{1, K.F.ipl, K.F.ept, K.F.fp32}].push_back(r);
+    if (K.mg) cls[{2, K.L.ept_m, K.M.fp32, K.L.fp32}].push_back(r);
+    else if (K.fused) cls[{1, K.F.ipl, K.F.ept, K.F.fp32}].push_back(r);
     else cls[{0, K.L.ns, K.L.ept_m, K.L.fp32}].push_back(r);
   }
   // sizes
@@ -101,6 +104,7 @@ size_t plan_shared(const std::vector<Run*>& runs, int which, std::vector<Plan>& 
   for (auto& kv : cls) {
     Plan p;
     p.fused = std::get<0>(kv.first) == 1;
+    p.mg = std::get<0>(kv.first) == 2;
     p.rs = kv.second;
     std::vector<int> nm, nv, nf;
     for (Run* r : p.rs) {
@@ -123,8 +127,10 @@ size_t plan_shared(const std::vector<Run*>& runs, int which, std::vector<Plan>& 
       p.o_fgroups = take(sizeof(FGroup) * p.rs.size());
       p.o_bf = take(sizeof(int2) * p.bf.size());
     }
-    // room for the block maps over unfinished groups (krylov_solve)
-    p.o_compact = take(sizeof(int2) * (p.bm.size() + p.bv.size() + p.bf.size()));
+    if (p.mg) p.o_mgroups = take(sizeof(MGroup) * p.rs.size());
+    // room for the block maps over unfinished groups (krylov_solve; multigrid
+    // solves, whose runs end within a few iterations of each other, have none)
+    if (!p.mg) p.o_compact = take(sizeof(int2) * (p.bm.size() + p.bv.size() + p.bf.size()));
     plans.push_back(std::move(p));
   }
   return std::max<size_t>(bytes, 256);
@@ -157,9 +163,10 @@ std::vector<Shared> make_shared(const std::vector<Run*>& runs, int which, hipStr
     for (Run* r : p.rs) {
       const KSet& own = set_of(*r, which);
       S.h_groups.push_back(own.h_groups[0]);
-      last = std::max(last, own.last_iters);
-      us = std::max(us, own.us_per_launch);
-      up = std::max(up, own.us_per_poll);
+      const Pace& pace = own.pace[p.mg ? 1 : 0];
+      last = std::max(last, pace.last_iters);
+      us = std::max(us, pace.us_per_launch);
+      up = std::max(up, pace.us_per_poll);
     }
     std::memcpy(host.data() + p.o_groups, S.h_groups.data(), sizeof(KGroup) * p.rs.size());
     std::memcpy(host.data() + p.o_bm, p.bm.data(), sizeof(int2) * p.bm.size());
@@ -179,8 +186,18 @@ std::vector<Shared> make_shared(const std::vector<Run*>& runs, int which, hipStr
                   (int)p.bv.size(),
                   fold};
     S.d_poll = reinterpret_cast<KState*>(base + p.o_poll);
-    S.d_compact = reinterpret_cast<int2*>(base + p.o_compact);
-    S.compact_cap = (int)(p.bm.size() + p.bv.size() + p.bf.size());
+    if (!p.mg) {
+      S.d_compact = reinterpret_cast<int2*>(base + p.o_compact);
+      S.compact_cap = (int)(p.bm.size() + p.bv.size() + p.bf.size());
+    } else {
+      for (Run* r : p.rs) S.h_mgroups.push_back(r->set_p.h_mgroups[0]);
+      std::memcpy(host.data() + p.o_mgroups, S.h_mgroups.data(), sizeof(MGroup) * p.rs.size());
+      S.mg = true;
+      S.M.groups = reinterpret_cast<const MGroup*>(base + p.o_mgroups);
+      S.M.fp32 = p.rs[0]->set_p.M.fp32;
+      for (int k = 0; k < MG_SLOTS; ++k)
+        for (Run* r : p.rs) S.M.nblocks[k] = std::max(S.M.nblocks[k], r->set_p.M.nblocks[k]);
+    }
     if (p.fused) {
       size_t lds = 0;
       for (Run* r : p.rs) {
@@ -197,9 +214,7 @@ std::vector<Shared> make_shared(const std::vector<Run*>& runs, int which, hipStr
                     (int)p.bf.size(), lds};
       S.F.ipl = F0.ipl;
     }
-    S.last_iters = last;
-    S.us_per_launch = us;
-    S.us_per_poll = up;
+    S.now() = Pace{last, us, up};
     std::copy(std::begin(set_of(*p.rs[0], which).kid), std::end(set_of(*p.rs[0], which).kid),
               std::begin(S.kid));
     out.push_back(std::move(sh));
@@ -219,6 +234,7 @@ void solve_shared(const std::vector<Run*>& runs, int which, KMethod m, hipStream
   std::unique_ptr<DevBuf> buf;
   std::vector<Shared> sets = make_shared(runs, which, s, buf, mem);
   KTimer none;
+  std::vector<Run*> again;   // multigrid solves that failed
   for (Shared& sh : sets) {
     int check_every = 1 << 30;
     for (Run* r : sh.owner) check_every = std::min(check_every, r->prm.check_every);
@@ -236,9 +252,7 @@ void solve_shared(const std::vector<Run*>& runs, int which, KMethod m, hipStream
     krylov_solve(s, sh.S, m, check_every, hs, pin, none, mem.dev == nullptr);
     for (size_t g = 0; g < sh.owner.size(); ++g) {
       Run* r = sh.owner[g];
-      set_of(*r, which).last_iters = sh.S.last_iters;
-      set_of(*r, which).us_per_launch = sh.S.us_per_launch;
-      set_of(*r, which).us_per_poll = sh.S.us_per_poll;
+      set_of(*r, which).now() = sh.S.now();
       const int ns = sh.S.h_groups[g].nsys;
       std::vector<KState> mine(hs.begin() + g * GMAX, hs.begin() + g * GMAX + ns);
       int code = IPCS_OK;
@@ -247,6 +261,11 @@ void solve_shared(const std::vector<Run*>& runs, int which, KMethod m, hipStream
         if (code == IPCS_OK && c != IPCS_OK) code = c;
       }
       rc[r] = code;
+      if (sh.S.mg && code != IPCS_OK) again.push_back(r);
+      if (which == 0) {
+        r->mom_it = 0;
+        for (const KState& k : mine) r->mom_it = std::max(r->mom_it, k.it);
+      }
       if (which != 1 || !r->mixed) fill_stats_solve(mine, ns, which + 1, st[r]);
       else if (st[r]) {
         st[r]->it_p += mine[0].it;
@@ -254,6 +273,10 @@ void solve_shared(const std::vector<Run*>& runs, int which, KMethod m, hipStream
       }
     }
   }
+  if (again.empty()) return;
+  // repeated by the Jacobi form (Run::poisson_cg)
+  for (Run* r : again) r->prepare_jacobi();
+  solve_shared(again, which, m, s, rc, st, mem);
 }
 
 }  // namespace
@@ -317,13 +340,14 @@ static void refine_shared(const std::vector<Run*>& runs, hipStream_t s, std::map
     // each pass sizes its polls from the same pass of the run's last step
     for (Run* r : inner) {
       const int k = ir[r].outer - 1;
-      r->set_p.last_iters = k < Run::kIrHist ? r->ir_last[k] : 0;
+      r->choose_poisson_cg();
+      if (!r->set_p.mg) r->set_p.now().last_iters = k < Run::kIrHist ? r->ir_last[k] : 0;
     }
     std::map<Run*, int> rin;
     solve_shared(inner, 1, KMethod::PCG, s, rin, st, mem);
     for (Run* r : inner) {
       const int k = ir[r].outer - 1;
-      if (k < Run::kIrHist) r->ir_last[k] = r->set_p.last_iters;
+      if (!r->set_p.mg && k < Run::kIrHist) r->ir_last[k] = r->set_p.now().last_iters;
     }
     active.clear();
     for (Run* r : inner) {

@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "mesh.hpp"
+
 namespace ipcs {
 
 constexpr int BLOCK = 256;        // threads per block of small utility kernels
@@ -135,6 +137,27 @@ struct FGroup {
   const uint16_t* hlcol;
   const void* hval;
   double* y[2];
+};
+
+// Multigrid preconditioner of one pressure Poisson system (mesh.hpp,
+// MgHierarchy) on the device: the products in order, each y = X x with X in CSR
+// (FP64 values, or FP32: MLaunch::fp32) and its blocks. The vectors of
+// neighbouring levels sit end to end in three buffers, so that a product over
+// several levels reads and writes one array. The last product's blocks write
+// the partial sums of r.z into part_z (nz of them).
+struct MgStep {
+  const int32_t* rp;
+  const int32_t* col;
+  const void* val;
+  const MgJob* job;
+  const double* x;
+  double* y;
+  int32_t njob, pad;
+};
+struct MGroup {
+  MgStep st[MG_SLOTS];
+  double* part_z;
+  int32_t nz, pad;
 };
 
 // Row-owner assembly inputs (see mesh.hpp)
@@ -293,6 +316,22 @@ void fcg_gather_values(hipStream_t s, bool fp32, int64_t nent, const int32_t* sr
                        const void* val, void* out);
 void fcg_gather_dinv(hipStream_t s, int64_t n, const int32_t* perm, const double* dinv,
                      double* out);
+
+// Multigrid-preconditioned CG (kernels_mg.hpp) over the groups of a KLaunch
+// (one system each); groups[i] belongs to the KLaunch's group i. nblocks[s]:
+// the most blocks any group has in product s (0 skips it); a launch takes that
+// many for every group, and the ones a smaller group has no job for end at
+// once (no map of blocks, whose room a batch without allocation would have to
+// find). A launch set of one group carries host copies of its group.
+struct MLaunch {
+  const MGroup* groups = nullptr;
+  int fp32 = 0;
+  int nblocks[MG_SLOTS] = {};
+  MGroup one{};
+  KGroup kone{};
+};
+void mg_apply(hipStream_t s, const KLaunch& L, const MLaunch& M, int par);   // stop test, z = B r, r.z
+void mg_update(hipStream_t s, const KLaunch& L, const MLaunch& M, int par);  // p, s, x, r from z, w = A z
 
 // Fields and right-hand sides (kernels_fields.hip)
 void eval_velocity(hipStream_t s, int dim, const Builtin& bi, const double* x, int64_t n,

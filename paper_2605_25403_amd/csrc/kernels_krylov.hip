@@ -866,3 +866,5 @@ void gather_states(hipStream_t s, const KLaunch& L, KState* out) {
 }
 
 }  // namespace ipcs
+
+#include "kernels_mg.hpp"

@@ -82,6 +82,52 @@ struct PartSell {
   std::vector<int32_t> hsrc;        // [hnent]
 };
 
+// One sparse product y = X x of the multigrid preconditioner (amg.hpp) in CSR,
+// with its blocks: rows [row0, row1) taken by one block of 256 threads, 2^lg
+// lanes per row.
+struct MgJob {
+  int32_t row0, row1, lg, pad;
+};
+// Array whose elements start uninitialized: large ones are first touched by
+// the threads that fill them.
+template <class T>
+struct RawVec {
+  std::unique_ptr<T[]> p;
+  size_t n = 0;
+  void alloc(size_t k) {
+    p.reset(new T[k]);
+    n = k;
+  }
+  size_t size() const { return n; }
+  T* data() { return p.get(); }
+  const T* data() const { return p.get(); }
+  T& operator[](size_t i) { return p[i]; }
+  const T& operator[](size_t i) const { return p[i]; }
+};
+struct MgProduct {
+  int64_t n = 0;
+  std::vector<int32_t> rp;
+  RawVec<int32_t> col;
+  RawVec<double> val;
+  std::vector<MgJob> jobs;
+};
+
+// The preconditioner B of the pressure Poisson CG as products (amg.hpp), base
+// level 0 (products 0, 2, 4) or 1 (all five); r_k the residual and e_k the
+// correction of level k, L the last level:
+//   0: base 0: [r_1; ..; r_L] from r_0          base 1: r_1 from r_0
+//   1:                                                  [r_2; ..; r_L] from r_1
+//   2: base 0: [e_1; ..; e_L] from [r_1; ..]    base 1: [e_2; ..] from [r_2; ..]
+//   3:                                                  e_1 from [r_1; e_2; ..; e_L]
+//   4: base 0: z from [r_0; e_1; ..; e_L]       base 1: z from [r_0; e_1]
+constexpr int MG_SLOTS = 5;
+struct MgHierarchy {
+  int64_t n = 0;                  // unknowns of the finest level
+  int levels = 0, base = 0;
+  int64_t nbase = 0, below = 0;   // unknowns of the base level and of all levels below it
+  MgProduct st[MG_SLOTS];
+};
+
 // The Taylor-Hood pair fixes the two spaces. Names keep the P2-P1 pair's
 // vocabulary: "2" is the velocity space, "1" the pressure space.
 //   P2-P1 (triangles, tetrahedra): velocity P2 (vertices and edge midpoints),
@@ -133,10 +179,16 @@ struct Mesh {
   // coordinates, built on first use for each part size and kept with the mesh
   // (depth 2: with the second halo ring, for two CG iterations per launch)
   std::shared_ptr<const PartSell> parts11(int rows_max, int depth = 1) const;
+  // multigrid preconditioner of the pressure stiffness matrix, built on first
+  // use and kept with the mesh; null where aggregation does not coarsen it
+  std::shared_ptr<const MgHierarchy> multigrid() const;
 
  private:
   mutable std::mutex parts_mu;
   mutable std::vector<std::shared_ptr<const PartSell>> parts_cache;
+  mutable std::mutex mg_mu;
+  mutable bool mg_built = false;
+  mutable std::shared_ptr<const MgHierarchy> mg_cache;
 };
 
 // SELL-64 layout of a CSR pattern (padding repeats a row's last column)

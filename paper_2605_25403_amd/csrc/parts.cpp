@@ -14,6 +14,7 @@
 #include <mutex>
 #include <numeric>
 
+#include "amg.hpp"
 #include "common.hpp"
 #include "mesh.hpp"
 
@@ -228,6 +229,20 @@ std::shared_ptr<const PartSell> Mesh::parts11(int rows_max, int depth) const {
   auto q = build_parts(p11, e11, xp.data(), dim, rows_max, depth);
   parts_cache.push_back(q);
   return q;
+}
+
+std::shared_ptr<const MgHierarchy> Mesh::multigrid() const {
+  std::lock_guard<std::mutex> lk(mg_mu);
+  if (!mg_built) {
+    if (n1 > nv) {   // P2 pressure
+      amg::Csr P = amg::p1_to_p2(*this);
+      mg_cache = amg::build(amg::pressure_stiffness(*this), &P);
+    } else {
+      mg_cache = amg::build(amg::pressure_stiffness(*this), nullptr);
+    }
+    mg_built = true;
+  }
+  return mg_cache;
 }
 
 }  // namespace ipcs

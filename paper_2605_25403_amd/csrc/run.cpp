@@ -240,10 +240,15 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
     for (int g = 0; g < S.L.ngroups; ++g)
       for (int j = 0; j < S.h_groups[g].nsys; ++j) f(hs[g * GMAX + j]);
   };
-  const bool fused = m == KMethod::PCG && S.fused;
+  const bool mg = m == KMethod::PCG && S.mg;
+  const bool fused = m == KMethod::PCG && S.fused && !mg;
   int ipl = fused ? S.F.ipl : 1;   // iterations per launch
   auto iterate = [&](int par) {
-    if (fused) {
+    if (mg) {
+      mg_apply(s, S.L, S.M, par);
+      pcg_spmv_only(s, S.L);
+      mg_update(s, S.L, S.M, par);
+    } else if (fused) {
       T.run(s, S.kid[0], [&] { fcg_iter(s, S.F, par); });
     } else if (m == KMethod::PCG) {
       T.run(s, S.kid[0], [&] { pcg_spmv_only(s, S.L); });
@@ -280,7 +285,7 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
   const KLaunch L_full = S.L;
   const FLaunch F_full = S.F;
   auto compact = [&]() {
-    if (!S.d_compact || S.L.ngroups < 2) return;
+    if (!S.d_compact || S.L.ngroups < 2 || mg) return;
     std::vector<int> nm(S.L.ngroups, 0), nv(S.L.ngroups, 0), nf(S.L.ngroups, 0);
     int tm = 0;
     for (int g = 0; g < S.L.ngroups; ++g) {
@@ -327,8 +332,8 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
   fetch();
   const int every = std::max(1, check_every);
   const int least =
-      S.us_per_launch > 0.0 && S.us_per_poll > 0.0
-          ? std::max(1, std::min(every, (int)std::ceil(S.us_per_poll / S.us_per_launch)))
+      S.now().us_per_launch > 0.0 && S.now().us_per_poll > 0.0
+          ? std::max(1, std::min(every, (int)std::ceil(S.now().us_per_poll / S.now().us_per_launch)))
           : every;
   bool restarted = false;
   int tail = 0;   // polls made in the unknown tail of the solve
@@ -358,15 +363,19 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
       // iterations are unknown: chunks (of launches) grow geometrically from
       // the least one
       int chunk;
-      if (restarted || launched >= S.last_iters) {
+      if (mg && launched == 0) {
+        // one more: a converged system's check is the next iteration's first
+        // kernel, and the rest of that iteration only reads the status
+        chunk = std::max(least, S.now().last_iters + 1);
+      } else if (restarted || launched >= S.now().last_iters) {
         chunk = least << std::min(tail, 10);
         ++tail;
       } else if (launched == 0 && S.L.ngroups == 1) {
         // (sets of several runs halve from the start: their runs end at
         // different counts, and a poll is where finished ones leave the launches)
-        chunk = std::max(least, (S.last_iters - std::max(least * ipl, S.last_iters / 16)) / ipl);
+        chunk = std::max(least, (S.now().last_iters - std::max(least * ipl, S.now().last_iters / 16)) / ipl);
       } else {
-        chunk = std::max(least, (S.last_iters - launched) / 2 / ipl);
+        chunk = std::max(least, (S.now().last_iters - launched) / 2 / ipl);
       }
       chunk = std::max(1, std::min(chunk, (rem + ipl - 1) / ipl));
       if (burst(true, [&] {
@@ -423,7 +432,7 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
   }
   int iters = 0;
   each([&](const KState& k) { iters = std::max(iters, k.it); });
-  S.last_iters = iters;   // the poll schedule of the next solve of this set
+  S.now().last_iters = iters;   // the poll schedule of the next solve of this set
   S.L = L_full;           // the finish covers every group
   S.F = F_full;
   // the stream has synchronized (last fetch): every recorded event is done
@@ -432,7 +441,7 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
     HIP_OK(hipEventElapsedTime(&ms, ev[2 * k], ev[2 * k + 1]));
     busy_ms += ms;
   }
-  if (timed_launches > 0) S.us_per_launch = 1000.0 * busy_ms / timed_launches;
+  if (timed_launches > 0) S.now().us_per_launch = 1000.0 * busy_ms / timed_launches;
   if (nburst > 1) {
     double gaps = 0.0;
     for (int k = 1; k < nburst; ++k) {
@@ -440,7 +449,7 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
       HIP_OK(hipEventElapsedTime(&ms, ev[2 * k - 1], ev[2 * k]));
       gaps += ms;
     }
-    S.us_per_poll = 1000.0 * gaps / (nburst - 1);
+    S.now().us_per_poll = 1000.0 * gaps / (nburst - 1);
   }
   if (fused) fcg_finish(s, S.F);
   else ksys_finish(s, S.L);
@@ -472,6 +481,7 @@ void Run::sizes_from_mesh() {
   ne11 = m.e11.nent;
   ne12 = m.e12.nent;
   choose_poisson_form();
+  choose_preconditioner();
 }
 
 // Row blocks of the convection assembly (row-owner and local-sum passes) are
@@ -522,6 +532,72 @@ void Run::choose_poisson_form() {
   for (int p = 0; p < q->nparts; ++p)
     most_slices = std::max(most_slices, q->slice_ptr[p + 1] - q->slice_ptr[p]);
   f_blk_ok = most_slices <= FBLK_SL;
+}
+
+// The Poisson CG takes the multigrid preconditioner where the parameters leave
+// the form open and the system has more than kMgRows rows. Pressure phase on
+// both sides, Jacobi against multigrid: 64^2 (4,225 rows) 1.42 / 0.55 ms,
+// 512^2 17.3 / 1.3 ms (1,600 / 20 iterations), 64^3 8.0 / 1.9 ms, P3-P2 on
+// 256^2 27.1 / 1.4 ms. The line keeps the gain near twofold and leaves the
+// smallest systems, at most about 170 Jacobi iterations, without a hierarchy.
+constexpr int64_t kMgRows = 2560;
+void Run::choose_preconditioner() {
+  mgh.reset();
+  if (prm.poisson_part_rows != 0 || prm.poisson_s != 0 || n1 <= kMgRows) return;
+  mgh = mesh->multigrid();
+  // the update's blocks re-read one partial sum per block of the last product
+  if (mgh && (int64_t)mgh->st[MG_SLOTS - 1].jobs.size() > KNB_MAX) mgh.reset();
+}
+
+void Run::upload_multigrid() {
+  const MgHierarchy& h = *mgh;
+  MGroup g;
+  std::memset(&g, 0, sizeof(g));
+  for (int k = 0; k < MG_SLOTS; ++k) {
+    const MgProduct& p = h.st[k];
+    if (p.jobs.empty()) continue;
+    const size_t nnz = p.col.size();
+    HIP_OK(hipMemcpyAsync(mg_rp[k], p.rp.data(), sizeof(int32_t) * p.rp.size(),
+                          hipMemcpyHostToDevice, stream));
+    HIP_OK(hipMemcpyAsync(mg_col[k], p.col.data(), sizeof(int32_t) * nnz, hipMemcpyHostToDevice,
+                          stream));
+    HIP_OK(hipMemcpyAsync(mg_jobs[k], p.jobs.data(), sizeof(MgJob) * p.jobs.size(),
+                          hipMemcpyHostToDevice, stream));
+    if (mixed) {
+      std::vector<float> f(nnz);
+      for (size_t q = 0; q < nnz; ++q) f[q] = (float)p.val[q];
+      HIP_OK(hipMemcpyAsync(mg_val[k], f.data(), sizeof(float) * nnz, hipMemcpyHostToDevice,
+                            stream));
+      HIP_OK(hipStreamSynchronize(stream));   // f goes away
+    } else {
+      HIP_OK(hipMemcpyAsync(mg_val[k], p.val.data(), sizeof(double) * nnz, hipMemcpyHostToDevice,
+                            stream));
+    }
+    g.st[k].rp = mg_rp[k];
+    g.st[k].col = mg_col[k];
+    g.st[k].val = mg_val[k];
+    g.st[k].job = mg_jobs[k];
+  }
+  // inputs and outputs (mesh.hpp, MgHierarchy)
+  double *a = mg_buf[0], *b = mg_buf[1], *c = mg_buf[2], *z = kv1 + n1;
+  const bool two = h.base == 1;
+  const double* x[MG_SLOTS] = {a, b, c, b, a};
+  double* y[MG_SLOTS] = {two ? b : c, c, two ? b + h.nbase : a + n1, a + n1, z};
+  for (int k = 0; k < MG_SLOTS; ++k) {
+    g.st[k].x = x[k];
+    g.st[k].y = y[k];
+    g.st[k].njob = (int32_t)h.st[k].jobs.size();
+    set_p.M.nblocks[k] = g.st[k].njob;
+  }
+  g.part_z = mg_part;
+  g.nz = (int32_t)h.st[MG_SLOTS - 1].jobs.size();
+  set_p.M.groups = mgroup;
+  set_p.M.fp32 = mixed ? 1 : 0;
+  set_p.M.one = g;
+  set_p.M.kone = set_p.h_groups[0];
+  set_p.h_mgroups = {g};
+  HIP_OK(hipMemcpyAsync(mgroup, set_p.h_mgroups.data(), sizeof(MGroup), hipMemcpyHostToDevice,
+                        stream));
 }
 
 void Run::layout(Carver& c) {
@@ -640,6 +716,21 @@ void Run::layout(Carver& c) {
       f_y = c.take<double>(10 * n1);
     }
     fgroup = c.take<FGroup>(1);
+  }
+  if (mgh) {
+    for (int k = 0; k < MG_SLOTS; ++k) {
+      const MgProduct& p = mgh->st[k];
+      if (p.jobs.empty()) continue;
+      mg_rp[k] = c.take<int32_t>(p.n + 1);
+      mg_col[k] = c.take<int32_t>((int64_t)p.col.size());
+      mg_val[k] = c.take<char>((int64_t)p.val.size() * vsz);
+      mg_jobs[k] = c.take<MgJob>((int64_t)p.jobs.size());
+    }
+    mg_buf[0] = c.take<double>(n1 + (mgh->base ? mgh->nbase : mgh->below));
+    mg_buf[1] = c.take<double>(mgh->base ? mgh->nbase + mgh->below : 1);
+    mg_buf[2] = c.take<double>(mgh->below);
+    mg_part = c.take<double>((int64_t)mgh->st[MG_SLOTS - 1].jobs.size());
+    mgroup = c.take<MGroup>(1);
   }
   spart = c.take<double>(8192 * 2);
   scnt = c.take<uint32_t>(4);
@@ -813,12 +904,14 @@ void Run::setup_solvers() {
       g.nsys = 1;
       g.sptr = sp11;
       g.col = col11;
-      g.val = Kp;
+      // multigrid CG: the FP64 matrix in both forms, the residual at the head
+      // of the finest product's input
+      g.val = mgh ? Kp64 : Kp;
       g.dinv = dinvKp;
       KVecs& V = g.v[0];
       V.b = mixed ? rIR : rP;
       V.x = mixed ? dIR : dP;
-      V.r = kv1;
+      V.r = mgh ? mg_buf[0] : kv1;
       V.u = kv1 + n1;
       V.p = kv1 + 2 * n1;
       V.s = kv1 + 3 * n1;
@@ -870,12 +963,12 @@ void Run::setup_solvers() {
                           hipMemcpyHostToDevice, stream));
     HIP_OK(hipMemcpyAsync(bmap_v[gi], maps_v[gi].data(), sizeof(int2) * maps_v[gi].size(),
                           hipMemcpyHostToDevice, stream));
-    S.L = KLaunch{kgroups + gi,      1, grp[gi].nsys, kept_m_for(grp[gi].n, grp[gi].nsys), mixed ? 1 : 0,
+    S.L = KLaunch{kgroups + gi,      1, grp[gi].nsys, kept_m_for(grp[gi].n, grp[gi].nsys),
+                  mixed && !(gi == 1 && mgh) ? 1 : 0,
                   bmap_m[gi],        (int)maps_m[gi].size(),
                   bmap_v[gi],        (int)maps_v[gi].size(),
                   fold_for(grp[gi].n, grp[gi].nsys)};
     S.d_poll = poll + gi * GMAX;
-    S.last_iters = 0;
   };
   mk(set_mom, 0);
   mk(set_p, 1);
@@ -936,6 +1029,7 @@ void Run::setup_solvers() {
       set_p.F.one = f;
     }
   }
+  if (mgh) upload_multigrid();
   const int kid_mom[4] = {IPCS_KERNEL_BICG_SPMV, IPCS_KERNEL_BICG_UPDATE_S,
                           IPCS_KERNEL_BICG_SPMV_T, IPCS_KERNEL_BICG_UPDATE_X};
   for (int k = 0; k < 4; ++k) set_mom.kid[k] = kid_mom[k];
@@ -1154,6 +1248,7 @@ void Run::asm_phase() {
 // solve: dP = 0, or the previous step's dP (FP64 form: dP keeps it; mixed
 // form: the first refinement pass's correction d starts there, dP = 0).
 void Run::pressure_rhs() {
+  choose_poisson_cg();
   // r is a difference of terms that cancel exactly at a discrete steady
   // state; an r no larger than a bound on its own rounding error is treated
   // as zero (dP = 0): on the solve's state in the FP64 form, in the
@@ -1229,6 +1324,8 @@ int Run::phase(int which, ipcs_step_stats* st) {
       rc = krylov_solve(stream, set_mom, KMethod::BICG, prm.check_every, hs, pinned,
                         timer);
       fill_stats_solve(hs, dim, 1, st);
+      mom_it = 0;
+      for (int c = 0; c < dim; ++c) mom_it = std::max(mom_it, hs[c].it);
       HIP_OK(hipEventRecord(ev[2], stream));
       if (rc != IPCS_OK) {
         if (st) st->failed_solve = 1;
@@ -1419,6 +1516,32 @@ void Run::export_values(int pattern, const void* dev, int vbytes, double* out) {
       out[P.rowptr[i] + k] = h[S.index(i, k)];
 }
 
+// One CG solve of the Poisson set from the current start. A multigrid solve
+// that fails (a mesh its hierarchy does not suit, a tolerance out of reach) is
+// repeated from zero by the Jacobi form, whose status is then the result.
+int Run::poisson_cg(std::vector<KState>& hs) {
+  int rc = krylov_solve(stream, set_p, KMethod::PCG, prm.check_every, hs, pinned, timer);
+  if (rc == IPCS_OK || !set_p.mg) return rc;
+  prepare_jacobi();
+  return krylov_solve(stream, set_p, KMethod::PCG, prm.check_every, hs, pinned, timer);
+}
+
+// BiCGStab's path through a long momentum solve depends on the last bit of its
+// input: from about 45 iterations on, pressures that differ by 1e-15 lead to
+// tentative velocities that differ by all that the tolerance leaves open, and
+// to 1e-9 of the pressure a step later (at 40 and fewer: 1e-13).
+// After such a solve the pressure stays with the Jacobi form, bit for bit the
+// increment that it has always given, so that a run does not move by more than
+// its solves resolve when the preconditioner changes.
+constexpr int kMgMomentum = 40;
+void Run::choose_poisson_cg() { set_p.mg = mgh && mom_it <= kMgMomentum; }
+
+// The next solve of the Poisson set is the Jacobi form's, from x = 0.
+void Run::prepare_jacobi() {
+  set_p.mg = false;
+  HIP_OK(hipMemsetAsync(set_p.h_groups[0].v[0].x, 0, sizeof(double) * n1, stream));
+}
+
 // Pressure Poisson solve (eq. (9), second line). FP64 form: one Jacobi-CG
 // solve of Kp dP = r to tol_p. Mixed form: iterative refinement in FP64 on
 // the FP64 Kp: res = r - Kp dP (projected to zero sum), stop when
@@ -1426,8 +1549,7 @@ void Run::export_values(int pattern, const void* dev, int vbytes, double* out) {
 // matrix (FP64 vectors and sums) to a loose relative tolerance and add d.
 int Run::pressure_solve(std::vector<KState>& hs, ipcs_step_stats* st) {
   if (!mixed) {
-    const int rc = krylov_solve(stream, set_p, KMethod::PCG, prm.check_every, hs,
-                                pinned, timer);
+    const int rc = poisson_cg(hs);
     fill_stats_solve(hs, 1, 2, st);
     return rc;
   }
@@ -1472,9 +1594,10 @@ int Run::pressure_solve(std::vector<KState>& hs, ipcs_step_stats* st) {
     last_tol = tol_in;
     set_tolerance(stream, set_p.L, tol_in * tol_in);
     if (outer > 0 || !warm_p()) HIP_OK(hipMemsetAsync(dIR, 0, sizeof(double) * n1, stream));
-    set_p.last_iters = outer < kIrHist ? ir_last[outer] : 0;
-    rc = krylov_solve(stream, set_p, KMethod::PCG, prm.check_every, hs, pinned, timer);
-    if (outer < kIrHist) ir_last[outer] = set_p.last_iters;
+    choose_poisson_cg();
+    if (!set_p.mg) set_p.now().last_iters = outer < kIrHist ? ir_last[outer] : 0;
+    rc = poisson_cg(hs);
+    if (!set_p.mg && outer < kIrHist) ir_last[outer] = set_p.now().last_iters;
     inner_total += hs[0].it;
     checks_total += hs[0].nchecks;
     if (rc == IPCS_E_BREAKDOWN) {

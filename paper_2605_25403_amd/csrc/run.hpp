@@ -63,6 +63,14 @@ struct KTimer {
   void drain();   // the stream must have synchronized
 };
 
+// What a solve of a set took, from which the next one sizes its polls.
+struct Pace {
+  int last_iters = 0;          // iterations
+  double us_per_launch = 0.0;  // device time per iteration launch (0: none yet)
+  double us_per_poll = 0.0;    // device idle time per status poll
+};
+constexpr int kMgIters = 18;   // expected iterations of a first multigrid solve
+
 // Host view of a set of Krylov groups solved by the same launches.
 struct KSet {
   KLaunch L{};
@@ -71,11 +79,15 @@ struct KSet {
   bool fused = false;
   FLaunch F{};
   std::vector<FGroup> h_fgroups;
+  // this solve takes the multigrid-preconditioned CG (kernels_mg.hpp) instead
+  // of the Jacobi forms above; L serves its start, product and polling
+  bool mg = false;
+  MLaunch M{};
+  std::vector<MGroup> h_mgroups;
   std::vector<KGroup> h_groups;
   KState* d_poll = nullptr;    // [ngroups * GMAX] polling copies of the states
-  int last_iters = 0;          // iterations the previous solve took (poll schedule)
-  double us_per_launch = 0.0;  // device time per iteration launch in the previous solve (0: none)
-  double us_per_poll = 0.0;    // device idle time per status poll in the previous solve
+  Pace pace[2] = {{}, {kMgIters, 0.0, 0.0}};   // Jacobi, multigrid
+  Pace& now() { return pace[mg ? 1 : 0]; }
   // kernel ids for timing: PCG {spmv, update} (fused: {iteration}),
   // BiCGStab {v, s, t, x}; -1: none
   int kid[4] = {-1, -1, -1, -1};
@@ -211,6 +223,15 @@ struct Run {
   void* f_hval = nullptr;
   double* f_y = nullptr;       // [2][5][n1]
   FGroup* fgroup = nullptr;
+  // multigrid preconditioner of the pressure Poisson CG (null: Jacobi only)
+  std::shared_ptr<const MgHierarchy> mgh;
+  int32_t *mg_rp[MG_SLOTS] = {}, *mg_col[MG_SLOTS] = {};
+  void* mg_val[MG_SLOTS] = {};
+  MgJob* mg_jobs[MG_SLOTS] = {};
+  double* mg_buf[3] = {};      // [r_0 | e ..], [r_1 | e ..], [r ..] (mesh.hpp)
+  double* mg_part = nullptr;
+  int mom_it = 0;              // this step's momentum iterations (most of any component)
+  MGroup* mgroup = nullptr;
   double* spart = nullptr;    // scratch partials for one-off reductions [8192*2]
   uint32_t* scnt = nullptr;
   double* scal = nullptr;     // [8] device scalars: 0 mean(r), 1 mean(dP), 2 mean(P)
@@ -239,6 +260,8 @@ struct Run {
   void set_precision();   // mixed and vsz from prm.precision
   void sizes_from_mesh();
   void choose_poisson_form();
+  void choose_preconditioner();
+  void upload_multigrid();
   void layout(Carver& c);
   // convection in two passes (cell-batched local matrices, then their
   // row-owner sum): 3D, and the P3-P2 pair in 2D
@@ -276,6 +299,10 @@ struct Run {
   // host-side CSR values (FP64) of a device SELL matrix of value size vbytes
   void export_values(int pattern, const void* dev, int vbytes, double* out);
   int pressure_solve(std::vector<KState>& hs, ipcs_step_stats* st);
+  int poisson_cg(std::vector<KState>& hs);
+  void prepare_jacobi();
+  // the Poisson CG of this step: multigrid, or Jacobi after a long momentum solve
+  void choose_poisson_cg();
 };
 
 // Where a batch step keeps its shared-launch descriptors and status staging.

@@ -73,6 +73,7 @@ KSet& set_of(Run& r, int which) {
 // descriptors in the solve's descriptor space.
 struct Plan {
   bool fused = false, mg = false;
+  SmallForm small;
   std::vector<Run*> rs;
   std::vector<int2> bm, bv, bf;
   size_t o_mgroups = 0;
@@ -82,13 +83,16 @@ struct Plan {
 // Plans the shared sets for system set `which` (0 momentum, 1 Poisson,
 // 2 correction) of the given runs; returns the bytes their descriptors take.
 size_t plan_shared(const std::vector<Run*>& runs, int which, std::vector<Plan>& plans) {
+  // one-block solves: (3 + width, ns, rows per thread, value type);
   // multigrid Poisson sets: (2, rows per thread, preconditioner's and matrix's
   // value types); fused Poisson sets: (1, iterations per launch, rows per
   // thread, value type); others: (0, ns, ept_m, value type)
   std::map<std::tuple<int, int, int, int>, std::vector<Run*>> cls;
   for (Run* r : runs) {
     const KSet& K = set_of(*r, which);
-    if (K.mg) cls[{2, K.L.ept_m, K.M.fp32, K.L.fp32}].push_back(r);
+    if (K.small.rows)
+      cls[{3 + K.small.width, K.L.ns, K.small.rows, K.L.fp32}].push_back(r);
+    else if (K.mg) cls[{2, K.L.ept_m, K.M.fp32, K.L.fp32}].push_back(r);
     else if (K.fused) cls[{1, K.F.ipl, K.F.ept, K.F.fp32}].push_back(r);
     else cls[{0, K.L.ns, K.L.ept_m, K.L.fp32}].push_back(r);
   }
@@ -105,6 +109,7 @@ size_t plan_shared(const std::vector<Run*>& runs, int which, std::vector<Plan>& 
     Plan p;
     p.fused = std::get<0>(kv.first) == 1;
     p.mg = std::get<0>(kv.first) == 2;
+    if (std::get<0>(kv.first) >= 3) p.small = set_of(*kv.second[0], which).small;
     p.rs = kv.second;
     std::vector<int> nm, nv, nf;
     for (Run* r : p.rs) {
@@ -130,7 +135,7 @@ size_t plan_shared(const std::vector<Run*>& runs, int which, std::vector<Plan>& 
     if (p.mg) p.o_mgroups = take(sizeof(MGroup) * p.rs.size());
     // room for the block maps over unfinished groups (krylov_solve; multigrid
     // solves, whose runs end within a few iterations of each other, have none)
-    if (!p.mg) p.o_compact = take(sizeof(int2) * (p.bm.size() + p.bv.size() + p.bf.size()));
+    if (!p.mg && !p.small.rows) p.o_compact = take(sizeof(int2) * (p.bm.size() + p.bv.size() + p.bf.size()));
     plans.push_back(std::move(p));
   }
   return std::max<size_t>(bytes, 256);
@@ -186,7 +191,10 @@ std::vector<Shared> make_shared(const std::vector<Run*>& runs, int which, hipStr
                   (int)p.bv.size(),
                   fold};
     S.d_poll = reinterpret_cast<KState*>(base + p.o_poll);
-    if (!p.mg) {
+    S.small = p.small;
+    if (p.small.rows) {
+      // no block maps to compact
+    } else if (!p.mg) {
       S.d_compact = reinterpret_cast<int2*>(base + p.o_compact);
       S.compact_cap = (int)(p.bm.size() + p.bv.size() + p.bf.size());
     } else {

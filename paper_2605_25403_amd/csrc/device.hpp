@@ -330,6 +330,24 @@ struct MLaunch {
   MGroup one{};
   KGroup kone{};
 };
+// Whole solves of small systems (kernels_small.hpp), one block per system. rows:
+// rows per thread of the set's groups; width: 8 or 20, the matrix rows kept in
+// registers (512 threads), or 0, streamed (1024 threads).
+struct SmallForm {
+  int rows = 0;   // 0: not a one-block solve
+  int width = 0;
+};
+constexpr int small_bs(int width) { return width ? 512 : 1024; }
+// most rows per thread: the registers of 512 threads hold 4 rows of 8 entries
+// beside their vectors, or 3 of 20 (FP32 values: 5)
+constexpr int small_rmax(int width, bool fp32) {
+  return width == 8 ? 4 : width == 20 && !fp32 ? 3 : 5;
+}
+// Most SELL entries of a streamed matrix: one CU reads about 150 GB/s, and at
+// this size its iteration costs what the four-kernel one does.
+constexpr int64_t SMALL_STREAM = 50000;
+SmallForm small_form(int64_t n, int maxw, int64_t nent, bool pcg, bool fp32);
+void small_solve(hipStream_t s, const KLaunch& L, bool pcg, SmallForm f, int nmax);
 void mg_apply(hipStream_t s, const KLaunch& L, const MLaunch& M, int par);   // stop test, z = B r, r.z
 void mg_update(hipStream_t s, const KLaunch& L, const MLaunch& M, int par);  // p, s, x, r from z, w = A z
 

@@ -868,3 +868,4 @@ void gather_states(hipStream_t s, const KLaunch& L, KState* out) {
 }  // namespace ipcs
 
 #include "kernels_mg.hpp"
+#include "kernels_small.hpp"

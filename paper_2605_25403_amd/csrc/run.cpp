@@ -266,6 +266,21 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
     else if (m == KMethod::PCG) pcg_start(s, S.L, mode, par, launched);
     else bicg_start(s, S.L, mode, par, launched);
   };
+  auto result = [&]() {
+    int rc = IPCS_OK;
+    each([&](const KState& k) {
+      const int c = status_to_code(k.status);
+      if (rc == IPCS_OK && c != IPCS_OK) rc = c;
+    });
+    return rc;
+  };
+  if (S.small.rows) {
+    int nmax = 0;
+    for (const KGroup& g : S.h_groups) nmax = std::max(nmax, (int)g.n);
+    small_solve(s, S.L, m == KMethod::PCG, S.small, nmax);
+    fetch();
+    return result();
+  }
   // groups with systems still iterating: the least remaining cap among them
   auto remaining = [&]() {
     int rem = -1;
@@ -453,12 +468,7 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
   }
   if (fused) fcg_finish(s, S.F);
   else ksys_finish(s, S.L);
-  int rc = IPCS_OK;
-  each([&](const KState& k) {
-    const int c = status_to_code(k.status);
-    if (rc == IPCS_OK && c != IPCS_OK) rc = c;
-  });
-  return rc;
+  return result();
 }
 
 // ------------------------------------------------------------------ layout
@@ -535,15 +545,21 @@ void Run::choose_poisson_form() {
 }
 
 // The Poisson CG takes the multigrid preconditioner where the parameters leave
-// the form open and the system has more than kMgRows rows. Pressure phase on
-// both sides, Jacobi against multigrid: 64^2 (4,225 rows) 1.42 / 0.55 ms,
-// 512^2 17.3 / 1.3 ms (1,600 / 20 iterations), 64^3 8.0 / 1.9 ms, P3-P2 on
-// 256^2 27.1 / 1.4 ms. The line keeps the gain near twofold and leaves the
-// smallest systems, at most about 170 Jacobi iterations, without a hierarchy.
-constexpr int64_t kMgRows = 2560;
+// the form open and the system is past one block's registers
+// (kernels_small.hpp): above kMgRows rows, or kMgWide where rows have more than
+// 8 entries. Pressure phase on both sides, Jacobi against multigrid: 64^2
+// (4,225 rows) 1.42 / 0.55 ms, 512^2 17.3 / 1.3 ms (1,600 / 20 iterations), 64^3
+// 8.0 / 1.9 ms, P3-P2 on 256^2 27.1 / 1.4 ms; of the wide ones, 12^3 (2,197
+// rows) 1.0 / 0.51 ms, P3-P2 on 21^2 (1,849) 1.39 / 0.51 and on 4^3 (729) 1.05 /
+// 0.56 ms, where fewer rows take fewer than 70 Jacobi iterations. Between one
+// block's 2,048 short rows and kMgRows the one-launch-per-iteration form stays,
+// at most 170 iterations, whose counts its two-kernel twin reproduces.
+constexpr int64_t kMgRows = 2560, kMgWide = 500;
 void Run::choose_preconditioner() {
   mgh.reset();
-  if (prm.poisson_part_rows != 0 || prm.poisson_s != 0 || n1 <= kMgRows) return;
+  if (prm.poisson_part_rows != 0 || prm.poisson_s != 0) return;
+  if (n1 <= (mesh->e11.maxw <= 8 ? kMgRows : kMgWide)) return;
+  if (small_form(n1, mesh->e11.maxw, mesh->e11.nent, true, false).width) return;
   mgh = mesh->multigrid();
   // the update's blocks re-read one partial sum per block of the last product
   if (mgh && (int64_t)mgh->st[MG_SLOTS - 1].jobs.size() > KNB_MAX) mgh.reset();
@@ -969,6 +985,10 @@ void Run::setup_solvers() {
                   bmap_v[gi],        (int)maps_v[gi].size(),
                   fold_for(grp[gi].n, grp[gi].nsys)};
     S.d_poll = poll + gi * GMAX;
+    // small systems whole in one block, unless the parameters name a Poisson form
+    const Sell& A = gi == 1 ? mesh->e11 : mesh->e22;
+    if (gi != 1 || (prm.poisson_part_rows == 0 && prm.poisson_s == 0 && !mgh))
+      S.small = small_form(grp[gi].n, A.maxw, A.nent, gi != 0, mixed && gi != 1);
   };
   mk(set_mom, 0);
   mk(set_p, 1);

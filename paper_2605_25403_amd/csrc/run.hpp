@@ -84,6 +84,9 @@ struct KSet {
   bool mg = false;
   MLaunch M{};
   std::vector<MGroup> h_mgroups;
+  // whole solves in one block per system (kernels_small.hpp; rows 0: the forms
+  // above)
+  SmallForm small;
   std::vector<KGroup> h_groups;
   KState* d_poll = nullptr;    // [ngroups * GMAX] polling copies of the states
   Pace pace[2] = {{}, {kMgIters, 0.0, 0.0}};   // Jacobi, multigrid

@@ -506,11 +506,15 @@ void ipcs_run_destroy(ipcs_run r);
  *   [[nu K + C(U) + N(U), G], [D, 0]] (dU, dP) = (F - (nu K + C(U)) U - G P, -D U),
  * N_ce = (phi_j d_e u_c, phi_i), boundary velocity rows and columns
  * eliminated (the iterates carry the Dirichlet data), by flexible GMRES with
- * the block upper-triangular preconditioner [[A, G], [0, -(1/nu) diag(Mp 1)]]:
- * A, the velocity block, applied by a loose inner Jacobi-BiCGStab solve. The
- * pressure is fixed by zero integral mean after each step. The start is the
- * Dirichlet data on the boundary and zero elsewhere, P = 0. All device work
- * runs in the caller's workspace on the given stream. */
+ * the block upper-triangular preconditioner [[A, G], [0, -Mp / nu]]: A, the
+ * velocity block, applied by two multigrid sweeps on nu K, Mp by Chebyshev
+ * steps (no inner iterations); where its cycles gain too little (convection
+ * dominates, or a short restart), from zero again with [[A, G],
+ * [0, -(1/nu) diag(Mp 1)]], A applied by a loose inner Jacobi-BiCGStab solve.
+ * lin_maxit bounds each of the two. The pressure is fixed by zero integral
+ * mean after each step. The start is the Dirichlet data on the boundary and
+ * zero elsewhere, P = 0. All device work runs in the caller's workspace on the
+ * given stream. */
 typedef struct ipcs_steady_s* ipcs_steady;
 typedef struct {
   double nu;            /* kinematic viscosity                                 */

@@ -265,10 +265,10 @@ inline int64_t aggregate(const Csr& A, const std::vector<double>& diag, double t
   return na;
 }
 
-// Inverse of the last level's matrix, made definite on the constants it does
-// not see (Kp 1 = 0, and P keeps constants on every level). False if the
+// Inverse of the last level's matrix; a singular one is made definite on the
+// constants it does not see (Kp 1 = 0, and P keeps constants on every level). False if the
 // matrix is not positive.
-inline bool coarse_inverse(const Csr& A, Csr& B) {
+inline bool coarse_inverse(const Csr& A, bool singular, Csr& B) {
   const int64_t n = A.n;
   std::vector<double> L(n * n, 0.0), inv(n * n, 0.0);
   double dm = 0.0;
@@ -277,7 +277,8 @@ inline bool coarse_inverse(const Csr& A, Csr& B) {
       L[i * n + A.col[q]] += A.val[q];
       if (A.col[q] == i) dm += A.val[q] / n;
     }
-  for (double& v : L) v += dm / n;
+  if (singular)
+    for (double& v : L) v += dm / n;
   for (int64_t j = 0; j < n; ++j) {          // Cholesky, rows of L
     for (int64_t i = j; i < n; ++i) {
       double s = L[i * n + j];
@@ -428,36 +429,50 @@ inline void make_jobs(const Csr& X, const std::vector<int64_t>& segs, std::vecto
   jobs.swap(out);
 }
 
-// Sparse matrix of the pressure space's stiffness form on the mesh, P1 or P2,
-// without the entries that cancel (right angles).
-inline Csr pressure_stiffness(const Mesh& m) {
-  const int d = m.dim, nl = m.nloc1, nvl = d + 1;
+// Row-owner maps of one space of the mesh (P1 or P2 elements).
+struct Space {
+  int64_t n;
+  int nloc;
+  const Pattern* pat;
+  const Incidence* inc;
+  const SlotMap* slots;
+};
+inline Space pressure_space(const Mesh& m) { return {m.n1, m.nloc1, &m.p11, &m.inc1, &m.s11}; }
+inline Space velocity_space(const Mesh& m) { return {m.n2, m.nloc2, &m.p22, &m.inc2, &m.s22}; }
+
+// Sparse matrix of a space's stiffness form on the mesh, P1 or P2, without the
+// entries that cancel (right angles). fixed (may be null): nodes whose rows
+// and columns keep their diagonal only.
+inline Csr stiffness(const Mesh& m, const Space& sp, const uint8_t* fixed) {
+  const int d = m.dim, nl = sp.nloc, nvl = d + 1;
+  const Pattern& pat = *sp.pat;
   const double mean = 1.0 / (d + 1), off = 1.0 / ((d + 1.0) * (d + 2.0));
   static const int e2[3][2] = {{1, 2}, {2, 0}, {0, 1}};
   static const int e3[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}};
   const int(*ed)[2] = d == 2 ? e2 : e3;
   RawVec<double> full;                    // values on the mesh's pattern
-  full.alloc(m.p11.nnz());
+  full.alloc(pat.nnz());
   Csr C;
-  C.n = C.m = m.n1;
+  C.n = C.m = sp.n;
   C.rp.assign(C.n + 1, 0);
   auto keep = [&](int64_t i, int32_t k, double big) {
-    return std::fabs(full[k]) > 1e-13 * big || m.p11.col[k] == i;
+    if (pat.col[k] == i) return true;
+    return std::fabs(full[k]) > 1e-13 * big && !(fixed && (fixed[i] || fixed[pat.col[k]]));
   };
   auto largest = [&](int64_t i) {
     double big = 0.0;
-    for (int32_t k = m.p11.rowptr[i]; k < m.p11.rowptr[i + 1]; ++k)
+    for (int32_t k = pat.rowptr[i]; k < pat.rowptr[i + 1]; ++k)
       big = std::max(big, std::fabs(full[k]));
     return big;
   };
   ranges(C.n, [&](int, int64_t lo, int64_t hi) {
     for (int64_t i = lo; i < hi; ++i) {
-      double* acc = full.data() + m.p11.rowptr[i];
-      std::fill(acc, full.data() + m.p11.rowptr[i + 1], 0.0);
-      for (int32_t q = m.inc1.ptr[i]; q < m.inc1.ptr[i + 1]; ++q) {
-        const int64_t cell = m.inc1.code[q] >> 5;
-        const int li = m.inc1.code[q] & 31;
-        const int32_t* vt = m.c2dp.data() + cell * nl;
+      double* acc = full.data() + pat.rowptr[i];
+      std::fill(acc, full.data() + pat.rowptr[i + 1], 0.0);
+      for (int32_t q = sp.inc->ptr[i]; q < sp.inc->ptr[i + 1]; ++q) {
+        const int64_t cell = sp.inc->code[q] >> 5;
+        const int li = sp.inc->code[q] & 31;
+        const int32_t* vt = m.c2dp.data() + cell * m.nloc1;   // its vertices lead
         // barycentric gradients from the edge vectors
         double E[3][3] = {}, g[4][3] = {}, det;
         for (int a = 0; a < d; ++a)
@@ -506,11 +521,11 @@ inline Csr pressure_stiffness(const Mesh& m) {
             s = 16.0 * (I(a[0], b[0]) * gg(a[1], b[1]) + I(a[0], b[1]) * gg(a[1], b[0]) +
                         I(a[1], b[0]) * gg(a[0], b[1]) + I(a[1], b[1]) * gg(a[0], b[0]));
           }
-          acc[m.s11.slot[(size_t)q * m.s11.stride + j]] += vol * s;
+          acc[sp.slots->slot[(size_t)q * sp.slots->stride + j]] += vol * s;
         }
       }
       const double big = largest(i);
-      for (int32_t k = m.p11.rowptr[i]; k < m.p11.rowptr[i + 1]; ++k)
+      for (int32_t k = pat.rowptr[i]; k < pat.rowptr[i + 1]; ++k)
         C.rp[i + 1] += keep(i, k, big) ? 1 : 0;
     }
   });
@@ -519,14 +534,42 @@ inline Csr pressure_stiffness(const Mesh& m) {
     for (int64_t i = lo; i < hi; ++i) {
       const double big = largest(i);
       int32_t at = C.rp[i];
-      for (int32_t k = m.p11.rowptr[i]; k < m.p11.rowptr[i + 1]; ++k)
+      for (int32_t k = pat.rowptr[i]; k < pat.rowptr[i + 1]; ++k)
         if (keep(i, k, big)) {
-          C.col[at] = m.p11.col[k];
+          C.col[at] = pat.col[k];
           C.val[at++] = full[k];
         }
     }
   });
   return C;
+}
+
+// P1 mass matrix in the SELL-64 layout of the pressure pattern (padding 0).
+inline std::vector<double> p1_mass_sell(const Mesh& m) {
+  std::vector<double> v(m.e11.nent, 0.0);
+  const int d = m.dim;
+  const double off = 1.0 / ((d + 1.0) * (d + 2.0));
+  ranges(m.n1, [&](int, int64_t lo, int64_t hi) {
+    for (int64_t i = lo; i < hi; ++i)
+      for (int32_t q = m.inc1.ptr[i]; q < m.inc1.ptr[i + 1]; ++q) {
+        const int32_t* vt = m.c2dp.data() + (int64_t)(m.inc1.code[q] >> 5) * m.nloc1;
+        const int li = m.inc1.code[q] & 31;
+        double E[3][3] = {};
+        for (int a = 0; a < d; ++a)
+          for (int b = 0; b < d; ++b)
+            E[a][b] = m.X[(size_t)vt[a + 1] * d + b] - m.X[(size_t)vt[0] * d + b];
+        const double det =
+            d == 2 ? E[0][0] * E[1][1] - E[0][1] * E[1][0]
+                   : E[0][0] * (E[1][1] * E[2][2] - E[1][2] * E[2][1]) -
+                         E[0][1] * (E[1][0] * E[2][2] - E[1][2] * E[2][0]) +
+                         E[0][2] * (E[1][0] * E[2][1] - E[1][1] * E[2][0]);
+        const double vol = std::fabs(det) / (d == 2 ? 2.0 : 6.0);
+        for (int j = 0; j <= d; ++j)
+          v[m.e11.index(i, m.s11.slot[(size_t)q * m.s11.stride + j])] +=
+              vol * off * (j == li ? 2.0 : 1.0);
+      }
+  });
+  return v;
 }
 
 constexpr int64_t kCoarsest = 200;       // last level: solved by its dense inverse
@@ -576,10 +619,51 @@ inline Csr p1_to_p2(const Mesh& m) {
   return P;
 }
 
+// P2 velocity nodes off the boundary from the vertices off the boundary, as
+// p1_to_p2; empty rows on the boundary. Empty (m = 0) without such vertices.
+inline Csr p1_to_velocity(const Mesh& m) {
+  std::vector<int32_t> inner(m.nv, -1), ends(2 * m.n2, -1);
+  int32_t ni = 0;
+  for (int64_t v = 0; v < m.nv; ++v)
+    if (!m.bmask[v]) inner[v] = ni++;
+  static const int e2[3][2] = {{1, 2}, {2, 0}, {0, 1}};
+  static const int e3[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}};
+  const int(*ed)[2] = m.dim == 2 ? e2 : e3;
+  for (int64_t c = 0; c < m.nc; ++c)
+    for (int j = m.dim + 1; j < m.nloc2; ++j)
+      for (int k = 0; k < 2; ++k)
+        ends[2 * (size_t)m.c2d[c * m.nloc2 + j] + k] =
+            m.c2dp[c * m.nloc1 + ed[j - m.dim - 1][k]];
+  Csr P;
+  P.n = m.n2;
+  P.m = ni;
+  P.rp.assign(P.n + 1, 0);
+  auto entries = [&](int64_t i, int32_t* c) {
+    int k = 0;
+    if (m.bmask[i]) return k;
+    if (i < m.nv) c[k++] = inner[i];
+    else
+      for (int e = 0; e < 2; ++e)
+        if (inner[ends[2 * i + e]] >= 0) c[k++] = inner[ends[2 * i + e]];
+    return k;
+  };
+  int32_t c[2];
+  for (int64_t i = 0; i < P.n; ++i) P.rp[i + 1] = entries(i, c);
+  allocate(P);
+  for (int64_t i = 0; i < P.n; ++i) {
+    const int k = entries(i, c);
+    for (int e = 0; e < k; ++e) {
+      P.col[P.rp[i] + e] = c[e];
+      P.val[P.rp[i] + e] = i < m.nv ? 1.0 : 0.5;
+    }
+  }
+  return P;
+}
+
 // The hierarchy's products for the symmetric matrix A (constants in its null
-// space), or null where aggregation does not coarsen it. P0 (may be null):
+// space if singular), or null where aggregation does not coarsen it. P0 (may be null):
 // the prolongator of the finest level, taken over.
-inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0) {
+inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0, bool singular) {
   std::vector<Level> lev;
   Csr B;
   double theta = 0.08;
@@ -591,8 +675,8 @@ inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0) {
       if (!(dg[i] > 0.0)) return nullptr;
       L.dinv[i] = 1.0 / dg[i];
     }
-    if (A.n <= kCoarsest) {
-      if (!coarse_inverse(A, B)) return nullptr;
+    if (A.n <= kCoarsest && !(lev.empty() && P0)) {
+      if (A.n == 0 || !coarse_inverse(A, singular, B)) return nullptr;
       L.A = std::move(A);
       lev.push_back(std::move(L));
       break;

@@ -348,6 +348,10 @@ constexpr int small_rmax(int width, bool fp32) {
 constexpr int64_t SMALL_STREAM = 50000;
 SmallForm small_form(int64_t n, int maxw, int64_t nent, bool pcg, bool fp32);
 void small_solve(hipStream_t s, const KLaunch& L, bool pcg, SmallForm f, int nmax);
+// out (nvec vectors at stride ld) = scale B r (+ add), r at the head of each
+// group's finest input (FP64 values)
+void mg_cycle(hipStream_t s, const MGroup* groups, int nvec, const int* nblocks, double scale,
+              const double* add, double* out, int64_t ld);
 void mg_apply(hipStream_t s, const KLaunch& L, const MLaunch& M, int par);   // stop test, z = B r, r.z
 void mg_update(hipStream_t s, const KLaunch& L, const MLaunch& M, int par);  // p, s, x, r from z, w = A z
 

@@ -202,7 +202,37 @@ __global__ void __launch_bounds__(KBS) k_mgcg_update(const KGroup* groups, const
   if (threadIdx.x == 0) G(g.part_v[par ^ 1])[g.nblk_v + lb] = rr[0];
 }
 
+// One product of the preconditioner by itself, for the vector of every group
+// (blockIdx.y). LAST: out[g * ld + i] = scale * value (+ add[g * ld + i]).
+template <bool LAST>
+__global__ void __launch_bounds__(KBS) k_mg_cycle(const MGroup* mgs, int slot, double scale,
+                                                  const double* add, double* out, int64_t ld) {
+  __shared__ double sh[KBS / 64];
+  const MgStep& S = mgs[blockIdx.y].st[slot];
+  if ((int)blockIdx.x >= S.njob) return;
+  const int64_t o = LAST ? (int64_t)blockIdx.y * ld : 0;
+  mg_job<double>(S, S.job[blockIdx.x], sh, [&](int i, double v) {
+    if (LAST) G(out)[o + i] = scale * v + (add ? G(add)[o + i] : 0.0);
+    else G(S.y)[i] = v;
+  });
+}
+
 // ------------------------------------------------------------------ launchers
+void mg_cycle(hipStream_t s, const MGroup* groups, int nvec, const int* nblocks, double scale,
+              const double* add, double* out, int64_t ld) {
+  for (int slot = 0; slot < MG_SLOTS; ++slot) {
+    if (nblocks[slot] == 0) continue;
+    const dim3 grid(nblocks[slot], nvec);
+    if (slot == MG_SLOTS - 1)
+      hipLaunchKernelGGL((k_mg_cycle<true>), grid, dim3(KBS), 0, s, groups, slot, scale, add, out,
+                         ld);
+    else
+      hipLaunchKernelGGL((k_mg_cycle<false>), grid, dim3(KBS), 0, s, groups, slot, scale, add, out,
+                         ld);
+    HIP_LAUNCH_OK();
+  }
+}
+
 template <int KIND, class VT>
 static void mg_launch(hipStream_t s, const KLaunch& L, const MLaunch& M, int slot, int par) {
   if (M.nblocks[slot] == 0) return;

@@ -140,6 +140,101 @@ k_prec_p(int64_t n1, const double* vp, const double* w, double nu, double* zp) {
   if (k < n1) zp[k] = -nu * vp[k] / w[k];
 }
 
+// Two Chebyshev steps on D^{-1} M for the consistent pressure mass matrix M
+// (eigenvalues in [1/2, (d + 2)/2], Wathen 1987), from x1 = d1 = D^{-1} v / theta:
+// d <- a d + b D^{-1} (v - M x), x <- x + d. FIRST forms x1 from v as it gathers;
+// the second step writes out = scale x.
+template <bool FIRST>
+__global__ void __launch_bounds__(SBS)
+k_mass_cheb(int64_t n, const int32_t* sp, const int32_t* col, const double* M, const double* dinv,
+            const double* v, double itheta, double a, double b, double* x, double* d, double scale,
+            double* out) {
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= n) return;
+  const int sl = (int)(r >> 6), w = (sp[sl + 1] - sp[sl]) >> 6;
+  const int base = sp[sl] + (int)(r & 63);
+  double s = 0.0;
+  for (int k = 0; k < w; k += 4) {
+    double m[4], g[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = base + 64 * (k + q < w ? k + q : w - 1);
+      const int c = col[e];
+      m[q] = k + q < w ? M[e] : 0.0;
+      g[q] = FIRST ? dinv[c] * v[c] * itheta : x[c];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s += m[q] * g[q];
+  }
+  const double x0 = FIRST ? dinv[r] * v[r] * itheta : x[r], d0 = FIRST ? x0 : d[r];
+  const double dn = a * d0 + b * dinv[r] * (v[r] - s);
+  if (FIRST) {
+    x[r] = x0 + dn;
+    d[r] = dn;
+  } else {
+    out[r] = scale * (x0 + dn);
+  }
+}
+
+// heads[c * ldh + i] = v_c[i] - (G_c zp)_i (v_c[i] on the boundary)
+// One launch for all components, which share the columns and zp's values; four
+// entries' loads go out before the first is used (the launch is one chain of
+// dependent loads: 9409 rows are 147 waves, less than one per CU).
+__global__ void __launch_bounds__(SBS)
+k_prec_rhs(int dim, int64_t n2, const int32_t* sp, const int32_t* col, const double* G0,
+           const double* G1, const double* G2, const uint8_t* bmask, const double* v,
+           const double* zp, double* heads, int64_t ldh) {
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= n2) return;
+  const int sl = (int)(r >> 6), w = (sp[sl + 1] - sp[sl]) >> 6;
+  const int base = sp[sl] + (int)(r & 63);
+  double s[3] = {0.0, 0.0, 0.0};
+  if (!bmask[r])
+    for (int k = 0; k < w; k += 4) {
+      double g[3][4], z[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool on = k + q < w;
+        const int e = base + 64 * (on ? k + q : w - 1);
+        z[q] = zp[col[e]];
+        g[0][q] = on ? G0[e] : 0.0;
+        g[1][q] = on ? G1[e] : 0.0;
+        g[2][q] = on && dim == 3 ? G2[e] : 0.0;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s[c] += g[c][q] * z[q];
+    }
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    if (c < dim) heads[c * ldh + r] = v[c * n2 + r] - s[c];
+}
+
+// heads[c * ldh + i] -= (A z)_(c n2 + i)
+// As above, eight entries at a time: the rows are the widest ones here.
+__global__ void __launch_bounds__(SBS)
+k_prec_resid(int64_t rows, int64_t n2, const int32_t* sp, const int32_t* col, const double* A,
+             const double* z, double* heads, int64_t ldh) {
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= rows) return;
+  const int sl = (int)(r >> 6), w = (sp[sl + 1] - sp[sl]) >> 6;
+  const int base = sp[sl] + (int)(r & 63);
+  double s = 0.0;
+  for (int k = 0; k < w; k += 8) {
+    double a[8], v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int e = base + 64 * (k + q < w ? k + q : w - 1);
+      a[q] = k + q < w ? A[e] : 0.0;
+      v[q] = z[col[e]];
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s += a[q] * v[q];
+  }
+  heads[(r / n2) * ldh + r % n2] -= s;
+}
+
 // v -= f * (*scal)
 __global__ void __launch_bounds__(SBS)
 k_sub_scaled(int64_t n, const double* scal, double f, double* v) {
@@ -210,6 +305,32 @@ void scale_inv_norm(hipStream_t s, int64_t n, const double* x, const double* nrm
 void prec_pressure(hipStream_t s, int64_t n1, const double* vp, const double* w, double nu,
                    double* zp) {
   launch(k_prec_p, dim3(grid(n1)), dim3(SBS), 0, s, n1, vp, w, nu, zp);
+}
+
+void mass_solve(hipStream_t s, int64_t n, int dim, const int32_t* sp, const int32_t* col,
+                const double* M, const double* dinv, const double* v, double scale, double* x,
+                double* d, double* out) {
+  const double lo = 0.5, hi = 0.5 * (dim + 2), theta = 0.5 * (lo + hi), delta = 0.5 * (hi - lo);
+  const double sigma = theta / delta;
+  double rho = 1.0 / sigma, rn = 1.0 / (2.0 * sigma - rho);
+  launch(k_mass_cheb<true>, dim3(grid(n)), dim3(SBS), 0, s, n, sp, col, M, dinv, v, 1.0 / theta,
+         rn * rho, 2.0 * rn / delta, x, d, scale, out);
+  rho = rn;
+  rn = 1.0 / (2.0 * sigma - rho);
+  launch(k_mass_cheb<false>, dim3(grid(n)), dim3(SBS), 0, s, n, sp, col, M, dinv, v, 1.0 / theta,
+         rn * rho, 2.0 * rn / delta, x, d, scale, out);
+}
+
+void prec_rhs(hipStream_t s, int dim, int64_t n2, const int32_t* sp, const int32_t* col,
+              const double* const* G, const uint8_t* bmask, const double* v, const double* zp,
+              double* heads, int64_t ldh) {
+  launch(k_prec_rhs, dim3(grid(n2)), dim3(SBS), 0, s, dim, n2, sp, col, G[0], G[1],
+         dim == 3 ? G[2] : G[0], bmask, v, zp, heads, ldh);
+}
+
+void prec_resid(hipStream_t s, int64_t rows, int64_t n2, const int32_t* sp, const int32_t* col,
+                const double* A, const double* z, double* heads, int64_t ldh) {
+  launch(k_prec_resid, dim3(grid(rows)), dim3(SBS), 0, s, rows, n2, sp, col, A, z, heads, ldh);
 }
 
 void sub_scaled(hipStream_t s, int64_t n, const double* scal, double f, double* v) {

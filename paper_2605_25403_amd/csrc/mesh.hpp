@@ -182,13 +182,16 @@ struct Mesh {
   // multigrid preconditioner of the pressure stiffness matrix, built on first
   // use and kept with the mesh; null where aggregation does not coarsen it
   std::shared_ptr<const MgHierarchy> multigrid() const;
+  // the same for the velocity's stiffness matrix with its boundary nodes
+  // eliminated (P2-P1 pair)
+  std::shared_ptr<const MgHierarchy> velocity_multigrid() const;
 
  private:
   mutable std::mutex parts_mu;
   mutable std::vector<std::shared_ptr<const PartSell>> parts_cache;
   mutable std::mutex mg_mu;
-  mutable bool mg_built = false;
-  mutable std::shared_ptr<const MgHierarchy> mg_cache;
+  mutable bool mg_built = false, mgv_built = false;
+  mutable std::shared_ptr<const MgHierarchy> mg_cache, mgv_cache;
 };
 
 // SELL-64 layout of a CSR pattern (padding repeats a row's last column)
@@ -196,6 +199,9 @@ void build_sell(const Pattern& P, Sell& S);
 
 std::shared_ptr<const PartSell> build_parts(const Pattern& P, const Sell& S, const double* X,
                                             int dim, int rows_max, int depth = 1);
+
+// P1 mass matrix in the SELL-64 layout of p11 (P2-P1 pair)
+std::vector<double> p1_mass_sell(const Mesh& m);
 
 // Builders. All throw ipcs::Error on invalid input.
 Mesh* build_unit_square(int nx, int ny, int pair = 0);

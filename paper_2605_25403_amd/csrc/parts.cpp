@@ -234,15 +234,27 @@ std::shared_ptr<const PartSell> Mesh::parts11(int rows_max, int depth) const {
 std::shared_ptr<const MgHierarchy> Mesh::multigrid() const {
   std::lock_guard<std::mutex> lk(mg_mu);
   if (!mg_built) {
-    if (n1 > nv) {   // P2 pressure
-      amg::Csr P = amg::p1_to_p2(*this);
-      mg_cache = amg::build(amg::pressure_stiffness(*this), &P);
-    } else {
-      mg_cache = amg::build(amg::pressure_stiffness(*this), nullptr);
-    }
+    amg::Csr A = amg::stiffness(*this, amg::pressure_space(*this), nullptr);
+    amg::Csr P;
+    if (n1 > nv) P = amg::p1_to_p2(*this);   // P2 pressure
+    mg_cache = amg::build(std::move(A), n1 > nv ? &P : nullptr, true);
     mg_built = true;
   }
   return mg_cache;
 }
+
+std::shared_ptr<const MgHierarchy> Mesh::velocity_multigrid() const {
+  std::lock_guard<std::mutex> lk(mg_mu);
+  if (!mgv_built) {
+    amg::Csr P = amg::p1_to_velocity(*this);
+    if (P.m > 0)
+      mgv_cache = amg::build(amg::stiffness(*this, amg::velocity_space(*this), bmask.data()), &P,
+                             false);
+    mgv_built = true;
+  }
+  return mgv_cache;
+}
+
+std::vector<double> p1_mass_sell(const Mesh& m) { return amg::p1_mass_sell(m); }
 
 }  // namespace ipcs

@@ -10,8 +10,16 @@
 // boundary velocity rows and columns eliminated (the iterates carry the
 // Dirichlet data, the increments vanish there), by flexible GMRES with the
 // block upper-triangular preconditioner [[A, G], [0, -S]]^{-1}: A the
-// velocity block of J, applied by a loose inner Jacobi-BiCGStab solve, and
-// S = (1/nu) diag(Mp 1) for the pressure Schur complement. The pressure is
+// velocity block of J and S = Mp / nu for the pressure Schur complement. A is
+// applied by two sweeps z += B (r - A z) of the multigrid cycle B of nu K
+// (amg.hpp), Mp by three Chebyshev steps on its consistent form: a fixed
+// preconditioner of some twenty launches, which takes 50 to 100 iterations
+// whatever the mesh where viscosity dominates: 48^2 squares at nu = 1 took 303
+// iterations with 11898 inner ones in 387 ms, and take 188 in 25 ms (130 us an
+// iteration, the chain of launches); 8^3 cubes 639 and 150 ms. Where an FGMRES
+// cycle gains less than a factor 30 (20^2 squares at nu = 0.02: 868 ms before,
+// 794 ms now with the cycle tried first; nu = 0.005: 6127 and 6017 ms), the Newton system is solved again with A by a
+// loose inner Jacobi-BiCGStab solve and S = (1/nu) diag(Mp 1). The pressure is
 // shifted to zero integral mean after every step.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -60,6 +68,18 @@ void maxpy(hipStream_t s, int64_t n, const double* V, int64_t ldv, const double*
 void scale_inv_norm(hipStream_t s, int64_t n, const double* x, const double* nrm2, double* y);
 void prec_pressure(hipStream_t s, int64_t n1, const double* vp, const double* w, double nu,
                    double* zp);
+// out = scale M^{-1} v to the accuracy of three Chebyshev steps (M the P1 mass
+// matrix, SELL-64, dinv its inverse diagonal; x, d: n doubles of work)
+void mass_solve(hipStream_t s, int64_t n, int dim, const int32_t* sp, const int32_t* col,
+                const double* M, const double* dinv, const double* v, double scale, double* x,
+                double* d, double* out);
+// heads[c ldh + i] = v_c - G_c zp off the boundary, v_c on it
+void prec_rhs(hipStream_t s, int dim, int64_t n2, const int32_t* sp, const int32_t* col,
+              const double* const* G, const uint8_t* bmask, const double* v, const double* zp,
+              double* heads, int64_t ldh);
+// heads -= A z (row c n2 + i of A at heads[c ldh + i])
+void prec_resid(hipStream_t s, int64_t rows, int64_t n2, const int32_t* sp, const int32_t* col,
+                const double* A, const double* z, double* heads, int64_t ldh);
 void sub_scaled(hipStream_t s, int64_t n, const double* scal, double f, double* v);
 void fill(hipStream_t s, int64_t n, double v, double* y);
 void copy_vec(hipStream_t s, int64_t n, const double* x, double* y);
@@ -81,7 +101,7 @@ struct Steady {
   Run run;                    // mesh data, K, D_c, G_c, w, forcing, Dirichlet data, U, P
   ipcs_steady_params sp{};
   int dim = 2;
-  int64_t n2 = 0, n1 = 0, nu_rows = 0, n = 0;
+  int64_t n2 = 0, n1 = 0, nu_rows = 0, n = 0, ne11 = 0;
   MonoPattern mj, ma;
   // device arrays (in the workspace after the run's own)
   int32_t *j_sp = nullptr, *j_col = nullptr, *j_src = nullptr;
@@ -101,6 +121,17 @@ struct Steady {
   int2 *bm = nullptr, *bv = nullptr;
   KState* poll = nullptr;
   KSet setA;
+  // multigrid preconditioner (null: the inner Jacobi solves only): products,
+  // buffers per component, P1 mass matrix
+  std::shared_ptr<const MgHierarchy> mgh;
+  int32_t *mg_rp[MG_SLOTS] = {}, *mg_col[MG_SLOTS] = {};
+  double* mg_val[MG_SLOTS] = {};
+  MgJob* mg_jobs[MG_SLOTS] = {};
+  double* mg_buf[3] = {};
+  MGroup* mg_groups = nullptr;
+  int mg_nblocks[MG_SLOTS] = {};
+  bool mg_off = false;   // a Newton step of this problem was past it
+  double *mass = nullptr, *dinvMp = nullptr, *mx = nullptr, *md = nullptr, *hcol = nullptr;
   KState* pinned = nullptr;
   hipEvent_t ev[2] = {};
   int64_t ws_run = 0;
@@ -119,6 +150,10 @@ struct Steady {
   // one Newton step; returns ||dx|| / ||x|| (x after the update)
   double newton_step(ipcs_steady_stats* st);
   int solve(ipcs_steady_stats* st);
+  // dx of J dx = R by the multigrid-preconditioned FGMRES; false if it does not
+  // get there (total then counts its iterations)
+  bool solve_multigrid(double beta0, int& total);
+  void upload_multigrid();
   void to_run();     // x -> the run's U, P (for read-back)
 };
 

@@ -63,8 +63,8 @@ namespace ipcs {
   const int lb = m_.y;
 
 // Row i of the group's SELL-64 matrix applied to NS gathered vectors:
-// acc[j] = sum_k A(i, col_k) * gath(j, col_k), in FP64 whatever the stored
-// value type VT. The slice width is uniform in the wavefront; the last chunk
+// acc[j] = sum_k A(i, col_k) * x_j(col_k), in FP64 whatever the stored value
+// type VT; gath(c, x) loads row c of every vector. The slice width is uniform in the wavefront; the last chunk
 // of eight re-reads entry w-1 and discards it.
 template <int NS, class VT, class GF>
 __device__ __forceinline__ void sell_row(const KGroup& g, int i, GF gath, double (&acc)[NS]) {
@@ -85,16 +85,35 @@ __device__ __forceinline__ void sell_row(const KGroup& g, int i, GF gath, double
       c[q] = col[base + 64 * kk];
       a[q] = (double)val[base + 64 * kk];
     }
-    double xv[NS][8];
+    double xv[8][NS];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) gath(c[q], xv[q]);
 #pragma unroll
     for (int j = 0; j < NS; ++j)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) xv[j][q] = gath(j, c[q]);
-#pragma unroll
-    for (int j = 0; j < NS; ++j)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc[j] += k + q < w ? a[q] * xv[j][q] : 0.0;
+      for (int q = 0; q < 8; ++q) acc[j] += k + q < w ? a[q] * xv[q][j] : 0.0;
   }
+}
+
+// Kernels of at least this many blocks (more than are resident at once) read
+// the status words before they issue their loads: iterations launched past
+// convergence then cost a launch instead of a pass over the matrix (48^3..64^3
+// cubes: 215 us each), and the words' latency is only paid by the first blocks.
+// Smaller ones issue their loads first.
+constexpr int kStatusFirst = 2048;
+
+// Row c of NS interleaved vectors, pairs as one 16-byte load.
+template <int NS>
+__device__ __forceinline__ void interleaved_row(const double* x, int c, double (&v)[NS]) {
+  typedef double pair __attribute__((ext_vector_type(2), aligned(8)));
+  const gptr<const double> r = G(x) + (size_t)c * NS;
+#pragma unroll
+  for (int j = 0; j + 1 < NS; j += 2) {
+    const pair p = *(gptr<const pair>)(r + j);
+    v[j] = p.x;
+    v[j + 1] = p.y;
+  }
+  if constexpr (NS % 2 == 1) v[NS - 1] = r[NS - 1];
 }
 
 template <int EPT>
@@ -129,7 +148,13 @@ __global__ void __launch_bounds__(KBS) k_start(const KGroup* groups, const int2*
       const int i = row_of<EPT>(lb, e);
       if (i >= g.n) continue;
       double ax[NS];
-      sell_row<NS, VT>(g, i, [&](int j, int c) { return G(g.v[j].x)[c]; }, ax);
+      sell_row<NS, VT>(
+          g, i,
+          [&](int c, double (&v)[NS]) {
+#pragma unroll
+            for (int j = 0; j < NS; ++j) v[j] = G(g.v[j].x)[c];
+          },
+          ax);
       const double di = G(g.dinv)[i];
 #pragma unroll
       for (int j = 0; j < NS; ++j) {
@@ -258,25 +283,35 @@ __device__ __forceinline__ void bicg5_totals(const KGroup& g, double (&t)[NS * 4
   load_partials<NS, 4>(g.part_m, g.nblk_m, t);
 }
 
-// One block per group: the totals of kernel KIND (0 PCG update, 1 BiCGStab
-// s-update, 2 BiCGStab x-update) into g.fold, read by every block of that
-// kernel in its folding form.
+// One block per group and total: the totals of kernel KIND (0 PCG update,
+// 1 BiCGStab s-update, 2 BiCGStab x-update) into g.fold, read by every block of
+// that kernel in its folding form. The totals do not depend on each other, and
+// each is summed in the order of load_partials, sixteen records a thread in
+// flight; one block for all NS * K of them was a chain of dependent loads.
 template <int KIND, int NS>
 __global__ void __launch_bounds__(KBS) k_fold(const KGroup* groups, int par) {
   const KGroup& g = groups[blockIdx.x];
-  constexpr int K = KIND == 0 ? 3 : KIND == 1 ? 2 : 4;
-  __shared__ double sh[(KBS / 64) * NS * K];
-  double t[NS * K];
-  if constexpr (KIND == 0) cg_update_totals<NS>(g, par, t);
-  else if constexpr (KIND == 1) bicg3_totals<NS>(g, par, t);
-  else bicg5_totals<NS>(g, t);
-  block_sum_t<KBS, NS * K>(t, sh);
-  if ((int)threadIdx.x < NS * K) {
-    double v = 0.0;
+  constexpr int K = KIND == 0 ? 3 : KIND == 1 ? 2 : 4, QC = 16;
+  __shared__ double sh[KBS / 64];
+  const int n = blockIdx.y, j = n / K, k = n % K;
+  const bool vec = KIND == 0 ? k < 2 : KIND == 1 && k == 1;   // of the last vector kernel
+  const int nb = vec ? g.nblk_v : g.nblk_m;
+  const gptr<const double> P =
+      G((const double*)(vec ? g.part_v[par] : g.part_m)) +
+      part_index(j, KIND == 0 ? (vec ? k : 0) : KIND == 1 ? 0 : k, nb, 0);
+  double t[1] = {0.0};
+  for (int q0 = 0; q0 * KBS < nb; q0 += QC) {
+    double x[QC];
 #pragma unroll
-    for (int n = 0; n < NS * K; ++n) v = n == (int)threadIdx.x ? t[n] : v;
-    G(g.fold)[threadIdx.x] = v;
+    for (int q = 0; q < QC; ++q) {
+      const int b = (int)threadIdx.x + (q0 + q) * KBS;
+      x[q] = P[b < nb ? b : nb - 1];
+    }
+#pragma unroll
+    for (int q = 0; q < QC; ++q) t[0] += (int)threadIdx.x + (q0 + q) * KBS < nb ? x[q] : 0.0;
   }
+  block_sum_t<KBS, 1>(t, sh);
+  if (threadIdx.x == 0) G(g.fold)[n] = t[0];
 }
 
 // ------------------------------------------------------------------ PCG (Chronopoulos-Gear)
@@ -291,11 +326,13 @@ __global__ void __launch_bounds__(KBS) k_cg_spmv(const KGroup* groups, const int
     run[j] = G(g.v[j].st)->status == KS_RUN;
     any |= run[j];
   }
+  if (g.nblk_m >= kStatusFirst && !any) return;
   double y[EPT][NS], ui[EPT][NS];
 #pragma unroll
   for (int e = 0; e < EPT; ++e) {
     const int i = row_clamp(row_of<EPT>(lb, e), g.n);
-    sell_row<NS, VT>(g, i, [&](int j, int c) { return G(g.v[j].u)[(size_t)c * NS]; }, y[e]);
+    sell_row<NS, VT>(
+          g, i, [&](int c, double (&v)[NS]) { interleaved_row<NS>(g.v[0].u, c, v); }, y[e]);
 #pragma unroll
     for (int j = 0; j < NS; ++j) ui[e][j] = G(g.v[j].u)[(size_t)i * NS];
   }
@@ -322,6 +359,7 @@ __global__ void __launch_bounds__(KBS) k_cg_update(const KGroup* groups, const i
   constexpr int EV = kept_v(NS);
   __shared__ double sh[(KBS / 64) * NS * 3];
   int status[NS];
+  bool live = false;
   double g_old[NS], a_old[NS], lim[NS];
 #pragma unroll
   for (int j = 0; j < NS; ++j) {
@@ -330,7 +368,9 @@ __global__ void __launch_bounds__(KBS) k_cg_update(const KGroup* groups, const i
     g_old[j] = st->sc[par ^ 1];
     a_old[j] = st->alpha[par ^ 1];
     lim[j] = st->tol2 * st->bb;
+    live |= status[j] == KS_RUN;
   }
+  if (FOLD && !live) return;   // many blocks: as for kStatusFirst
   double di[EV], xi[EV][NS], ri[EV][NS], pi[EV][NS], si[EV][NS],
       wi[EV][NS];
 #pragma unroll
@@ -442,15 +482,17 @@ __global__ void __launch_bounds__(KBS) k_bicg_spmv(const KGroup* groups, const i
   // block skips its loads (the iteration launched past convergence would
   // otherwise read the whole matrix); b2 issues its loads first, as the
   // systems' status is decided after it
-  if (WHICH == 1 && !any) return;
+  if ((WHICH == 1 || g.nblk_m >= kStatusFirst) && !any) return;
   double y[EPT][NS], rh[EPT][NS], si[EPT][NS];
 #pragma unroll
   for (int e = 0; e < EPT; ++e) {
     const int i = row_clamp(row_of<EPT>(lb, e), g.n);
     if (WHICH == 0)
-      sell_row<NS, VT>(g, i, [&](int j, int c) { return G(g.v[j].phat)[(size_t)c * NS]; }, y[e]);
+      sell_row<NS, VT>(
+          g, i, [&](int c, double (&v)[NS]) { interleaved_row<NS>(g.v[0].phat, c, v); }, y[e]);
     else
-      sell_row<NS, VT>(g, i, [&](int j, int c) { return G(g.v[j].shat)[(size_t)c * NS]; }, y[e]);
+      sell_row<NS, VT>(
+          g, i, [&](int c, double (&v)[NS]) { interleaved_row<NS>(g.v[0].shat, c, v); }, y[e]);
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
       rh[e][j] = G(g.v[j].u)[(size_t)i * NS];
@@ -488,6 +530,7 @@ __global__ void __launch_bounds__(KBS) k_bicg_3(const KGroup* groups, const int2
   constexpr int EV = kept_v(NS);
   __shared__ double sh[(KBS / 64) * NS * 2];
   int status[NS];
+  bool live = false;
   double rho[NS], lim[NS];
 #pragma unroll
   for (int j = 0; j < NS; ++j) {
@@ -495,7 +538,9 @@ __global__ void __launch_bounds__(KBS) k_bicg_3(const KGroup* groups, const int2
     status[j] = st->status;
     rho[j] = st->sc[par];
     lim[j] = st->tol2 * st->bb;
+    live |= status[j] == KS_RUN;
   }
+  if (FOLD && !live) return;   // many blocks: as for kStatusFirst
   double di[EV], ri[EV][NS], vi[EV][NS];
 #pragma unroll
   for (int e = 0; e < EV; ++e) {
@@ -776,7 +821,7 @@ void pcg_spmv_only(hipStream_t s, const KLaunch& L) {
 void pcg_update_only(hipStream_t s, const KLaunch& L, int par) {
   with_ns(L.ns, [&](auto N) {
     if (L.fold) {
-      hipLaunchKernelGGL((k_fold<0, NSV>), dim3(L.ngroups), dim3(KBS), 0, s, L.groups, par);
+      hipLaunchKernelGGL((k_fold<0, NSV>), dim3(L.ngroups, NSV * 3), dim3(KBS), 0, s, L.groups, par);
       HIP_LAUNCH_OK();
       launch(k_cg_update<NSV, true>, dim3(L.nblocks_v), dim3(KBS), 0, s, L.groups, L.bmap_v,
              par);
@@ -804,7 +849,7 @@ void bicg_spmv_only(hipStream_t s, const KLaunch& L) {
 void bicg_update_s_only(hipStream_t s, const KLaunch& L, int par) {
   with_ns(L.ns, [&](auto N) {
     if (L.fold) {
-      hipLaunchKernelGGL((k_fold<1, NSV>), dim3(L.ngroups), dim3(KBS), 0, s, L.groups, par);
+      hipLaunchKernelGGL((k_fold<1, NSV>), dim3(L.ngroups, NSV * 2), dim3(KBS), 0, s, L.groups, par);
       HIP_LAUNCH_OK();
       launch(k_bicg_3<NSV, true>, dim3(L.nblocks_v), dim3(KBS), 0, s, L.groups, L.bmap_v, par);
     } else {
@@ -826,7 +871,7 @@ void bicg_spmv_t_only(hipStream_t s, const KLaunch& L) {
 void bicg_update_x_only(hipStream_t s, const KLaunch& L, int par) {
   with_ns(L.ns, [&](auto N) {
     if (L.fold) {
-      hipLaunchKernelGGL((k_fold<2, NSV>), dim3(L.ngroups), dim3(KBS), 0, s, L.groups, par);
+      hipLaunchKernelGGL((k_fold<2, NSV>), dim3(L.ngroups, NSV * 4), dim3(KBS), 0, s, L.groups, par);
       HIP_LAUNCH_OK();
       launch(k_bicg_5<NSV, true>, dim3(L.nblocks_v), dim3(KBS), 0, s, L.groups, L.bmap_v, par);
     } else {

@@ -163,7 +163,7 @@ std::vector<Shared> make_shared(const std::vector<Run*>& runs, int which, hipStr
     Shared sh;
     sh.owner = p.rs;
     KSet& S = sh.S;
-    int last = 0;
+    int last = 0, solves = 0;
     double us = 0.0, up = 0.0;
     for (Run* r : p.rs) {
       const KSet& own = set_of(*r, which);
@@ -172,6 +172,7 @@ std::vector<Shared> make_shared(const std::vector<Run*>& runs, int which, hipStr
       last = std::max(last, pace.last_iters);
       us = std::max(us, pace.us_per_launch);
       up = std::max(up, pace.us_per_poll);
+      solves = std::max(solves, pace.solves);
     }
     std::memcpy(host.data() + p.o_groups, S.h_groups.data(), sizeof(KGroup) * p.rs.size());
     std::memcpy(host.data() + p.o_bm, p.bm.data(), sizeof(int2) * p.bm.size());
@@ -222,7 +223,7 @@ std::vector<Shared> make_shared(const std::vector<Run*>& runs, int which, hipStr
                     (int)p.bf.size(), lds};
       S.F.ipl = F0.ipl;
     }
-    S.now() = Pace{last, us, up};
+    S.now() = Pace{last, us, up, solves};
     std::copy(std::begin(set_of(*p.rs[0], which).kid), std::end(set_of(*p.rs[0], which).kid),
               std::begin(S.kid));
     out.push_back(std::move(sh));

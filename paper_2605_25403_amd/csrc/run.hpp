@@ -68,6 +68,7 @@ struct Pace {
   int last_iters = 0;          // iterations
   double us_per_launch = 0.0;  // device time per iteration launch (0: none yet)
   double us_per_poll = 0.0;    // device idle time per status poll
+  int solves = 0;              // solves since the set was made
 };
 constexpr int kMgIters = 18;   // expected iterations of a first multigrid solve
 

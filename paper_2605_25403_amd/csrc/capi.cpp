@@ -97,19 +97,58 @@ void check_params(const ipcs_params* p) {
 
 // The interface numbers velocity DOFs in listing order, the library
 // internally in coordinate order (mesh.hpp: v_out, v_in). These convert the
-// velocity-indexed data that crosses the interface.
-// out[c][v_out[i]] = in[c][i] for ncomp components of n2 values
-void vel_to_interface(const ipcs::Mesh& m, int ncomp, const double* in, double* out) {
-  const int64_t n = m.n2;
-  for (int c = 0; c < ncomp; ++c)
-    for (int64_t i = 0; i < n; ++i) out[c * n + m.v_out[i]] = in[c * n + i];
-}
+// velocity-indexed data that crosses the interface (fields on their way out:
+// copy_out_velocity).
 // out[c][i] = in[c][v_out[i]]
 void vel_to_internal(const ipcs::Mesh& m, int ncomp, const double* in, double* out) {
   const int64_t n = m.n2;
   for (int c = 0; c < ncomp; ++c)
     for (int64_t i = 0; i < n; ++i) out[c * n + i] = in[c * n + m.v_out[i]];
 }
+// Brings n doubles to the host through a pinned buffer of two halves: while the
+// caller's threads move one half on (put(first, count, values), ranges of a
+// chunk in parallel), the next chunk is copied into the other.
+template <class F>
+void read_back(hipStream_t s, const double* src, int64_t n, F put) {
+  struct Lease {
+    hipStream_t s;
+    double* p = ipcs::staging_take();
+    hipEvent_t ev[2] = {};
+    bool sent = false;
+    explicit Lease(hipStream_t st) : s(st) {}
+    ~Lease() {
+      if (sent) (void)hipStreamSynchronize(s);   // no copy outlives the lease
+      for (hipEvent_t e : ev)
+        if (e) (void)hipEventDestroy(e);
+      ipcs::staging_give(p);
+    }
+  } b(s);
+  constexpr int64_t H = ipcs::kStagingHalf;
+  auto copy = [&](int64_t c) {
+    const int64_t a = c * H, k = std::min(H, n - a);
+    b.sent = true;
+    HIP_OK(hipMemcpyAsync(b.p + (c & 1) * H, src + a, sizeof(double) * k, hipMemcpyDeviceToHost,
+                          s));
+    if (n > H) HIP_OK(hipEventRecord(b.ev[c & 1], s));
+  };
+  if (n > H)
+    for (hipEvent_t& e : b.ev) HIP_OK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  const int64_t chunks = (n + H - 1) / H;
+  if (chunks > 0) copy(0);
+  for (int64_t c = 0; c < chunks; ++c) {
+    if (c + 1 < chunks) copy(c + 1);
+    if (n > H) HIP_OK(hipEventSynchronize(b.ev[c & 1]));
+    else HIP_OK(hipStreamSynchronize(s));
+    const int64_t a = c * H, k = std::min(H, n - a);
+    const double* h = b.p + (c & 1) * H;
+    constexpr int64_t kPiece = 16384;
+    const int pieces = (int)((k + kPiece - 1) / kPiece);
+#pragma omp parallel for num_threads(std::min(pieces, 8)) schedule(static) if (pieces > 4)
+    for (int q = 0; q < pieces; ++q)
+      put(a + q * kPiece, std::min(kPiece, k - q * kPiece), h + q * kPiece);
+  }
+}
+
 // A CSR pattern (and values, if val) of the internal numbering in the
 // interface numbering: velocity rows and/or columns relabelled, rows in
 // interface order, columns ascending within each row.
@@ -469,8 +508,9 @@ int ipcs_step_phase(ipcs_run r, int32_t phase, ipcs_step_stats* stats) {
 
 static int copy_out(ipcs::Run& rr, const double* src, int64_t n, double* out, int64_t cap) {
   need(out != nullptr && cap >= n, "output buffer too small");
-  HIP_OK(hipMemcpyAsync(out, src, sizeof(double) * n, hipMemcpyDeviceToHost, rr.stream));
-  HIP_OK(hipStreamSynchronize(rr.stream));
+  read_back(rr.stream, src, n, [&](int64_t a, int64_t k, const double* h) {
+    std::memcpy(out + a, h, sizeof(double) * k);
+  });
   return IPCS_OK;
 }
 
@@ -478,10 +518,19 @@ static int copy_out(ipcs::Run& rr, const double* src, int64_t n, double* out, in
 static int copy_out_velocity(ipcs::Run& rr, const double* src, double* out, int64_t cap) {
   const int64_t n = (int64_t)rr.dim * rr.n2;
   need(out != nullptr && cap >= n, "output buffer too small");
-  std::vector<double> h((size_t)n);
-  HIP_OK(hipMemcpyAsync(h.data(), src, sizeof(double) * n, hipMemcpyDeviceToHost, rr.stream));
-  HIP_OK(hipStreamSynchronize(rr.stream));
-  vel_to_interface(*rr.mesh, rr.dim, h.data(), out);
+  const int32_t* to = rr.mesh->v_out.data();
+  const int64_t n2 = rr.n2;
+  read_back(rr.stream, src, n, [&](int64_t a, int64_t k, const double* h) {
+    int64_t i = a % n2;
+    double* o = out + (a - i);   // the component's values
+    for (int64_t q = 0; q < k; ++q) {
+      o[to[i]] = h[q];
+      if (++i == n2) {
+        i = 0;
+        o += n2;
+      }
+    }
+  });
   return IPCS_OK;
 }
 

@@ -166,6 +166,34 @@ void pinned_give(KState* p) {
   g_pinned_free.push_back(p);
 }
 
+static std::vector<double*> g_staging_free;   // under g_pinned_mu
+
+double* staging_take() {
+  {
+    std::lock_guard<std::mutex> lock(g_pinned_mu);
+    if (!g_staging_free.empty()) {
+      double* p = g_staging_free.back();
+      g_staging_free.pop_back();
+      return p;
+    }
+  }
+  double* p = nullptr;
+  HIP_OK(hipHostMalloc((void**)&p, sizeof(double) * 2 * kStagingHalf, hipHostMallocDefault));
+  return p;
+}
+
+void staging_give(double* p) {
+  if (!p) return;
+  {
+    std::lock_guard<std::mutex> lock(g_pinned_mu);
+    if ((int)g_staging_free.size() < kStagingKept) {
+      g_staging_free.push_back(p);
+      return;
+    }
+  }
+  (void)hipHostFree(p);
+}
+
 LaunchEvents*& launch_events() {
   thread_local LaunchEvents* slot = nullptr;
   return slot;

@@ -123,6 +123,17 @@ constexpr int kPinnedStates = 3 * GMAX;
 KState* pinned_take();
 void pinned_give(KState* p);
 
+// Pinned buffers of two halves of kStagingHalf doubles (8 MiB in all), through
+// which fields are read back: a copy into pageable memory is staged by the
+// runtime a little at a time, and the renumbering was one thread's (64^3 cubes,
+// 53 MB: 17 to 20 ms; through these, by up to eight threads, 1.5 to 3 ms; 512^2
+// squares, 19 MB: 2.1 and 0.5 ms).
+// Taken for one call; at most kStagingKept stay with the process between calls.
+constexpr int64_t kStagingHalf = 512 * 1024;
+constexpr int kStagingKept = 4;
+double* staging_take();
+void staging_give(double* p);
+
 // Rows per thread of matrix kernels for a group of n rows, and the block
 // counts of matrix / vector kernels (each at most KNB_MAX).
 int kept_m_for(int64_t n, int ns);

@@ -8,7 +8,8 @@
 //   B_k r = Lam_k r + Q_k B_{k+1} Q_k^T r,
 //   Lam = w (2 I - w D^{-1} A) D^{-1},  Q = S P,
 // P = (I - w_p D^{-1} A) T the smoothed prolongator over the aggregates T: the
-// cycle's smoothing steps move into Q, which is formed here once. Written out,
+// cycle's smoothing steps move into Q, which is formed here once (small plane
+// meshes: a V(2,2) cycle, Q = S^2 P, Lam = w (I + S + S^2 + S^3) D^{-1}). Written out,
 // the levels no longer wait for one another on the way down and up:
 //   e_k = Lam_k r_k with r_k = (Q_b ... Q_{k-1})^T r_b,
 //   B r_b = Lam_b r_b + sum_k (Q_b ... Q_{k-1}) e_k,
@@ -321,10 +322,32 @@ inline bool coarse_inverse(const Csr& A, bool singular, Csr& B) {
 }
 
 struct Level {
-  Csr A, Q;                        // matrix; Q = S P to the next level (empty on the last)
+  Csr A, Q;                        // matrix; Q = S^m P to the next level (empty on the last)
   std::vector<double> dinv;
   double omega = 0.0;
 };
+
+// X = P - w D^{-1} (A P), s = -w D^{-1}: the pattern of A P holds P's
+inline Csr smoothed(const Csr& P, const Csr& AP, const std::vector<double>& s) {
+  Csr Q;
+  Q.n = P.n;
+  Q.m = P.m;
+  Q.rp = AP.rp;
+  Q.col.alloc(AP.nnz());
+  Q.val.alloc(AP.nnz());
+  ranges(Q.n, [&](int, int64_t lo, int64_t hi) {
+    for (int64_t i = lo; i < hi; ++i)
+      for (int32_t q = AP.rp[i]; q < AP.rp[i + 1]; ++q) {
+        double v = s[i] * AP.val[q];
+        for (int32_t p = P.rp[i]; p < P.rp[i + 1]; ++p)
+          if (P.col[p] == AP.col[q]) v += P.val[p];
+        Q.col[q] = AP.col[q];
+        Q.val[q] = v;
+      }
+  });
+  return Q;
+}
+
 
 // [parts[0]; parts[1]; ..], part p's columns shifted by shift[p]
 inline Csr stack_rows(const std::vector<const Csr*>& parts, const std::vector<int32_t>& shift) {
@@ -377,8 +400,9 @@ inline Csr concat_cols(const std::vector<const Csr*>& parts, const std::vector<i
   return C;
 }
 
-// Lam = w (2 I - w D^{-1} A) D^{-1}
-inline Csr smoother(const Level& L) {
+// Lam = w (2 I - w D^{-1} A) D^{-1} = w (I + S) D^{-1}; for m = 2
+// w (I + S + S^2 + S^3) D^{-1}, which is Lam + S^2 Lam. Empty if it does not fit.
+inline Csr smoother(const Level& L, int m) {
   const Csr& A = L.A;
   Csr X;
   X.n = A.n;
@@ -395,7 +419,22 @@ inline Csr smoother(const Level& L) {
         if (j == i) X.val[q] += 2.0 * L.omega * L.dinv[i];
       }
   });
-  return X;
+  if (m == 1) return X;
+  std::vector<double> sc(A.n);
+  for (int64_t i = 0; i < A.n; ++i) sc[i] = -L.omega * L.dinv[i];
+  const Csr AX = product(A, X);
+  if (AX.n == 0) return Csr{};
+  const Csr SX = smoothed(X, AX, sc);
+  const Csr ASX = product(A, SX);
+  if (ASX.n == 0) return Csr{};
+  Csr Y = smoothed(SX, ASX, sc);           // its pattern holds X's
+  ranges(A.n, [&](int, int64_t lo, int64_t hi) {
+    for (int64_t i = lo; i < hi; ++i)
+      for (int32_t q = Y.rp[i]; q < Y.rp[i + 1]; ++q)
+        for (int32_t p = X.rp[i]; p < X.rp[i + 1]; ++p)
+          if (X.col[p] == Y.col[q]) Y.val[q] += X.val[p];
+  });
+  return Y;
 }
 
 // Blocks of a product: rows in runs of about kMgEntries entries, each run with
@@ -572,29 +611,15 @@ inline std::vector<double> p1_mass_sell(const Mesh& m) {
   return v;
 }
 
+// Two damped Jacobi steps before and after (m = 2) instead of one on matrices of
+// at most this many entries whose square has at most three times as many (plane
+// meshes). There an iteration is bound by its launches and not by the products'
+// entries: 64^2 squares take 12 iterations for 17 and 0.37 ms for 0.48; at 128^2
+// it is 13 for 18, 0.46 for 0.50 ms and 6 ms more of setup, at 165^2 0.63 ms
+// for 0.61; 21^3 cubes would take 14 for 20 with products three times as dense.
+constexpr int64_t kSweepsEntries = 50000;
 constexpr int64_t kCoarsest = 200;       // last level: solved by its dense inverse
 constexpr int64_t kComposeMax = 1200000; // entries of Q_0 times the levels below, for base 0
-
-// Q = P - w D^{-1} (A P): the pattern of A P holds P's
-inline Csr smoothed(const Csr& P, const Csr& AP, const std::vector<double>& s) {
-  Csr Q;
-  Q.n = P.n;
-  Q.m = P.m;
-  Q.rp = AP.rp;
-  Q.col.alloc(AP.nnz());
-  Q.val.alloc(AP.nnz());
-  ranges(Q.n, [&](int, int64_t lo, int64_t hi) {
-    for (int64_t i = lo; i < hi; ++i)
-      for (int32_t q = AP.rp[i]; q < AP.rp[i + 1]; ++q) {
-        double v = s[i] * AP.val[q];
-        for (int32_t p = P.rp[i]; p < P.rp[i + 1]; ++p)
-          if (P.col[p] == AP.col[q]) v += P.val[p];
-        Q.col[q] = AP.col[q];
-        Q.val[q] = v;
-      }
-  });
-  return Q;
-}
 
 // P2 pressure nodes from the vertices: a vertex keeps its value, an edge node
 // takes the mean of its two. The Galerkin matrix is then the P1 stiffness
@@ -667,6 +692,10 @@ inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0, bool singular) {
   std::vector<Level> lev;
   Csr B;
   double theta = 0.08;
+  const int sweeps = !P0 && A0.n > kCoarsest && A0.nnz() <= kSweepsEntries &&
+                             product(A0, A0).nnz() <= 3 * A0.nnz()
+                         ? 2
+                         : 1;
   for (Csr A = std::move(A0);; theta *= lev.size() == 1 && P0 ? 1.0 : 0.5) {
     Level L;
     std::vector<double> dg = diagonal(A);
@@ -709,6 +738,11 @@ inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0, bool singular) {
     const Csr AP = product(A, P);
     for (int64_t i = 0; i < A.n; ++i) s[i] = -L.omega * L.dinv[i];
     L.Q = smoothed(P, AP, s);
+    if (sweeps == 2) {
+      const Csr AQ = product(A, L.Q);
+      if (AQ.n == 0) return nullptr;
+      L.Q = smoothed(L.Q, AQ, s);
+    }
     Csr Ac = product(transpose(P), AP);
     if (P.n == 0 || AP.n == 0 || L.Q.n == 0 || Ac.n == 0) return nullptr;
     L.A = std::move(A);
@@ -731,12 +765,12 @@ inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0, bool singular) {
   std::vector<int64_t> segs{0};
   std::vector<const Csr*> rows, diags, parts;
   std::vector<int32_t> zero, block, shift{0};
-  const Csr lam = smoother(lev[base]);
+  const Csr lam = smoother(lev[base], sweeps);
   parts.push_back(&lam);
   for (int k = base + 1; k < nl; ++k) {
     if (from(k).n == 0) return nullptr;
     Rt[k] = transpose(from(k));
-    if (k + 1 < nl) Sm[k] = smoother(lev[k]);
+    if (k + 1 < nl) Sm[k] = smoother(lev[k], sweeps);
     rows.push_back(&Rt[k]);
     diags.push_back(k + 1 < nl ? &Sm[k] : &B);
     parts.push_back(&from(k));
@@ -763,7 +797,7 @@ inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0, bool singular) {
     put(4, up, {0, up.n});
   } else {
     Csr R1 = transpose(lev[0].Q);
-    const Csr lam0 = smoother(lev[0]);
+    const Csr lam0 = smoother(lev[0], sweeps);
     Csr up0 = concat_cols({&lam0, &lev[0].Q}, {0, (int32_t)h->n});
     if (up0.n == 0) return nullptr;
     put(0, R1, {0, R1.n});

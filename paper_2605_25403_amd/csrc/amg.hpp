@@ -618,6 +618,12 @@ inline std::vector<double> p1_mass_sell(const Mesh& m) {
 // it is 13 for 18, 0.46 for 0.50 ms and 6 ms more of setup, at 165^2 0.63 ms
 // for 0.61; 21^3 cubes would take 14 for 20 with products three times as dense.
 constexpr int64_t kSweepsEntries = 50000;
+// Most entries of the last product with w = A z beside z (A times its rows, 20
+// bytes an entry). It saves the launch of the product w = A z, 4 to 5 us: the
+// Poisson phase on 64^2 squares (264 thousand entries, 12 iterations) takes
+// 0.33 ms for 0.37, on 14^3 and 21^3 cubes (727 thousand, 19 iterations) 0.39
+// for 0.47 and 0.49 for 0.52; at 145^2 (857 thousand) 0.56 either way.
+constexpr int64_t kWithW = 750000;
 constexpr int64_t kCoarsest = 200;       // last level: solved by its dense inverse
 constexpr int64_t kComposeMax = 1200000; // entries of Q_0 times the levels below, for base 0
 
@@ -794,6 +800,25 @@ inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0, bool singular) {
   if (base == 0) {
     put(0, R, segs);
     put(2, Dg, segs);
+    // w = A z beside z, while the denser rows cost less than a launch of its own
+    // (an upper bound first: most large meshes are past the line)
+    Csr W;
+    if (singular && up.nnz() <= kWithW) W = product(lev[0].A, up);
+    if (W.n != 0 && W.nnz() <= kWithW) {
+      RawVec<double> z;
+      z.alloc(W.nnz());
+      ranges(W.n, [&](int, int64_t lo, int64_t hi) {
+        for (int64_t i = lo; i < hi; ++i)
+          for (int32_t q = W.rp[i]; q < W.rp[i + 1]; ++q) {
+            z[q] = 0.0;
+            for (int32_t p = up.rp[i]; p < up.rp[i + 1]; ++p)
+              if (up.col[p] == W.col[q]) z[q] = up.val[p];
+          }
+      });
+      h->st[4].val2 = std::move(W.val);
+      W.val = std::move(z);
+      up = std::move(W);
+    }
     put(4, up, {0, up.n});
   } else {
     Csr R1 = transpose(lev[0].Q);

@@ -168,6 +168,7 @@ std::vector<Shared> make_shared(const std::vector<Run*>& runs, int which, hipStr
     for (Run* r : p.rs) {
       const KSet& own = set_of(*r, which);
       S.h_groups.push_back(own.h_groups[0]);
+      if (p.mg) S.h_groups.back().no_w = own.M.with_w;
       const Pace& pace = own.pace[p.mg ? 1 : 0];
       last = std::max(last, pace.last_iters);
       us = std::max(us, pace.us_per_launch);
@@ -204,6 +205,8 @@ std::vector<Shared> make_shared(const std::vector<Run*>& runs, int which, hipStr
       S.mg = true;
       S.M.groups = reinterpret_cast<const MGroup*>(base + p.o_mgroups);
       S.M.fp32 = p.rs[0]->set_p.M.fp32;
+      S.M.with_w = 1;
+      for (Run* r : p.rs) S.M.with_w &= r->set_p.M.with_w;
       for (int k = 0; k < MG_SLOTS; ++k)
         for (Run* r : p.rs) S.M.nblocks[k] = std::max(S.M.nblocks[k], r->set_p.M.nblocks[k]);
     }

@@ -88,7 +88,8 @@ struct KGroup {
   const void* val;            // FP64 values, or FP32 (KLaunch::fp32)
   const double* dinv;         // Jacobi: 1 / diag(A)
   int32_t nblk_m, nblk_v;
-  int32_t maxit, pad;         // iteration cap of the group's systems
+  int32_t maxit;              // iteration cap of the group's systems
+  int32_t no_w;               // 1: k_cg_spmv leaves the group out (w comes with z)
   double* part_m;
   double* part_v[2];
   double* fold;               // [GMAX * KP] totals folded once from the records
@@ -144,11 +145,13 @@ struct FGroup {
 // (FP64 values, or FP32: MLaunch::fp32) and its blocks. The vectors of
 // neighbouring levels sit end to end in three buffers, so that a product over
 // several levels reads and writes one array. The last product's blocks write
-// the partial sums of r.z into part_z (nz of them).
+// the partial sums of r.z into part_z (nz of them), and with val2 those of z.w
+// behind them.
 struct MgStep {
   const int32_t* rp;
   const int32_t* col;
   const void* val;
+  const double* val2;         // last product: w = A z beside z; null: z alone
   const MgJob* job;
   const double* x;
   double* y;
@@ -326,6 +329,7 @@ void fcg_gather_dinv(hipStream_t s, int64_t n, const int32_t* perm, const double
 struct MLaunch {
   const MGroup* groups = nullptr;
   int fp32 = 0;
+  int with_w = 0;             // every group's last product forms w = A z too
   int nblocks[MG_SLOTS] = {};
   MGroup one{};
   KGroup kone{};

@@ -318,6 +318,7 @@ __global__ void __launch_bounds__(KBS) k_fold(const KGroup* groups, int par) {
 template <int NS, int EPT, class VT>
 __global__ void __launch_bounds__(KBS) k_cg_spmv(const KGroup* groups, const int2* bmap) {
   GROUP_HEAD(bmap)
+  if (g.no_w) return;
   __shared__ double sh[(KBS / 64) * NS];
   bool run[NS];
   bool any = false;

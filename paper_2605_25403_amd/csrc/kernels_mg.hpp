@@ -5,7 +5,8 @@
 // An iteration (Chronopoulos-Gear CG, u = z = B r in place of D^{-1} r):
 //   products: [||r||^2] stop test in the first one; z = B r (three or five
 //             sparse products, mesh.hpp MgHierarchy), partial r.z in the last
-//   spmv:     w = A z, partial z.w
+//   spmv:     w = A z, partial z.w (small hierarchies: formed by the last product
+//             from the same gathers, with A times its rows as second values)
 //   update:   [gamma = r.z, delta = z.w]; beta = gamma / gamma_old,
 //             alpha = gamma / (delta - beta gamma / alpha_old); p = z + beta p,
 //             s = w + beta s, x += alpha p, r -= alpha s, partial r.r
@@ -35,66 +36,81 @@ __device__ __forceinline__ double lanes_sum(double v) {
 }
 
 // Rows [job.row0, job.row1) of y = X x, 2^LG lanes per row (LG 8: the block).
-// put(row, sum) runs in one lane of each row.
-template <int LG, class VT, class F>
+// put(row, sum, sum2) runs in one lane of each row; TWO: sum2 is the row's sum
+// with the second values, else 0.
+template <int LG, bool TWO, class VT, class F>
 __device__ __forceinline__ void mg_rows(const MgStep& S, const MgJob& job, double* sh, F put) {
-  constexpr int LN = 1 << LG, PER = KBS >> LG, U = 4;
+  // (three at a time with second values: at four the shared launches of a
+  // batch lost a wave per SIMD)
+  constexpr int LN = 1 << LG, PER = KBS >> LG, U = TWO ? 3 : 4;
   const gptr<const int32_t> rp = G(S.rp), col = G(S.col);
   const gptr<const VT> val = G(static_cast<const VT*>(S.val));
+  const gptr<const double> val2 = G(S.val2);
   const gptr<const double> x = G(S.x);
   const int sub = (int)threadIdx.x & (LN - 1);
   for (int i0 = job.row0; i0 < job.row1; i0 += PER) {
     const int i = i0 + ((int)threadIdx.x >> LG);
     const int ic = i < job.row1 ? i : job.row0;
     const int b = rp[ic], e = rp[ic + 1];
-    double acc = 0.0;
+    double acc = 0.0, acc2 = 0.0;
     for (int k = b + sub; k < e; k += LN * U) {
       int c[U];
-      double a[U], v[U];
+      double a[U], a2[U], v[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int kk = k + u * LN < e ? k + u * LN : k;
         c[u] = col[kk];
         a[u] = (double)val[kk];
+        a2[u] = TWO ? val2[kk] : 0.0;
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) v[u] = x[c[u]];
 #pragma unroll
-      for (int u = 0; u < U; ++u) acc += k + u * LN < e ? a[u] * v[u] : 0.0;
+      for (int u = 0; u < U; ++u) {
+        acc += k + u * LN < e ? a[u] * v[u] : 0.0;
+        if (TWO) acc2 += k + u * LN < e ? a2[u] * v[u] : 0.0;
+      }
     }
     if constexpr (LG == 8) {
-      acc = wave_total(acc);
-      __syncthreads();
-      if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
-      __syncthreads();
-      acc = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+      auto block = [&](double t) {
+        t = wave_total(t);
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = t;
+        __syncthreads();
+        return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+      };
+      acc = block(acc);
+      if (TWO) acc2 = block(acc2);
     } else {
       acc = lanes_sum<LG>(acc);
+      if (TWO) acc2 = lanes_sum<LG>(acc2);
     }
-    if (sub == 0 && i < job.row1) put(i, acc);
+    if (sub == 0 && i < job.row1) put(i, acc, acc2);
   }
 }
 
-template <class VT, class F>
+template <bool TWO, class VT, class F>
 __device__ __forceinline__ void mg_job(const MgStep& S, const MgJob& job, double* sh, F put) {
   switch (job.lg) {   // the same for the whole block
-    case 2: mg_rows<2, VT>(S, job, sh, put); break;
-    case 3: mg_rows<3, VT>(S, job, sh, put); break;
-    case 4: mg_rows<4, VT>(S, job, sh, put); break;
-    case 5: mg_rows<5, VT>(S, job, sh, put); break;
-    case 6: mg_rows<6, VT>(S, job, sh, put); break;
-    default: mg_rows<8, VT>(S, job, sh, put); break;
+    case 2: mg_rows<2, TWO, VT>(S, job, sh, put); break;
+    case 3: mg_rows<3, TWO, VT>(S, job, sh, put); break;
+    case 4: mg_rows<4, TWO, VT>(S, job, sh, put); break;
+    case 5: mg_rows<5, TWO, VT>(S, job, sh, put); break;
+    case 6: mg_rows<6, TWO, VT>(S, job, sh, put); break;
+    default: mg_rows<8, TWO, VT>(S, job, sh, put); break;
   }
 }
 
 // One product. KIND 0: the first of an iteration, with the stop test on the
 // residual of the last update (block 0 of the group records it; a block that
 // finds the new status already there returns as the test would have it);
-// KIND 1: between; KIND 2: the last, with the partial sums of r.z.
+// KIND 1: between; KIND 2: the last, with the partial sums of r.z; KIND 3: the
+// last with w = A z from the same gathers, and the partial sums of r.z and z.w
+// (FP64 values in the mixed form too: w has to be A z for this z).
 template <int KIND, class VT>
 __device__ __forceinline__ void mg_product(const KGroup& g, const MGroup& m, const MgStep& S, int jb,
                                            int par) {
-  __shared__ double sh[KBS / 64];
+  __shared__ double sh[(KBS / 64) * 2];
   const gptr<const KState> st = G((const KState*)g.v[0].st);
   const int status = st->status;
   const MgJob job = S.job[jb];
@@ -119,16 +135,29 @@ __device__ __forceinline__ void mg_product(const KGroup& g, const MGroup& m, con
   } else if (status != KS_RUN) {
     return;
   }
-  if (KIND == 2) {
+  if (KIND == 3) {
+    double dot[2] = {0.0, 0.0};
+    mg_job<true, double>(S, job, sh, [&](int i, double z, double w) {
+      G(S.y)[i] = z;
+      G(g.v[0].w)[i] = w;
+      dot[0] += z * G(S.x)[i];   // the residual leads the input vector
+      dot[1] += z * w;
+    });
+    block_sum_t<KBS, 2>(dot, sh);
+    if (threadIdx.x == 0) {
+      G(m.part_z)[jb] = dot[0];
+      G(m.part_z)[m.nz + jb] = dot[1];
+    }
+  } else if (KIND == 2) {
     double dot[1] = {0.0};
-    mg_job<VT>(S, job, sh, [&](int i, double v) {
+    mg_job<false, VT>(S, job, sh, [&](int i, double v, double) {
       G(S.y)[i] = v;
-      dot[0] += v * G(S.x)[i];   // the residual leads the input vector
+      dot[0] += v * G(S.x)[i];
     });
     block_sum_t<KBS, 1>(dot, sh);
     if (threadIdx.x == 0) G(m.part_z)[jb] = dot[0];
   } else {
-    mg_job<VT>(S, job, sh, [&](int i, double v) { G(S.y)[i] = v; });
+    mg_job<false, VT>(S, job, sh, [&](int i, double v, double) { G(S.y)[i] = v; });
   }
 }
 
@@ -137,7 +166,10 @@ __global__ void __launch_bounds__(KBS) k_mg(const KGroup* groups, const MGroup* 
                                             int slot, int par) {
   const MGroup& m = mgs[blockIdx.y];
   if ((int)blockIdx.x >= m.st[slot].njob) return;
-  mg_product<KIND, VT>(groups[blockIdx.y], m, m.st[slot], blockIdx.x, par);
+  if (KIND == 2 && m.st[slot].val2)
+    mg_product<3, VT>(groups[blockIdx.y], m, m.st[slot], blockIdx.x, par);
+  else
+    mg_product<KIND, VT>(groups[blockIdx.y], m, m.st[slot], blockIdx.x, par);
 }
 
 // the same for one group, whose descriptors come with the launch
@@ -167,8 +199,10 @@ __global__ void __launch_bounds__(KBS) k_mgcg_update(const KGroup* groups, const
     zi[e] = G(V.u)[i];
   }
   double t[2];
-  load_partials<1, 1>(mgs[m_.x].part_z, mgs[m_.x].nz, t);
-  load_partials<1, 1>(g.part_m, g.nblk_m, t + 1);
+  const MGroup& m = mgs[m_.x];
+  const bool two = m.st[MG_SLOTS - 1].val2 != nullptr;
+  load_partials<1, 1>(m.part_z, m.nz, t);
+  load_partials<1, 1>(two ? m.part_z + m.nz : g.part_m, two ? m.nz : g.nblk_m, t + 1);
   block_sum_t<KBS, 2>(t, sh);
   if (status != KS_RUN) return;
   const bool lead = lb == 0 && threadIdx.x == 0;
@@ -211,7 +245,7 @@ __global__ void __launch_bounds__(KBS) k_mg_cycle(const MGroup* mgs, int slot, d
   const MgStep& S = mgs[blockIdx.y].st[slot];
   if ((int)blockIdx.x >= S.njob) return;
   const int64_t o = LAST ? (int64_t)blockIdx.y * ld : 0;
-  mg_job<double>(S, S.job[blockIdx.x], sh, [&](int i, double v) {
+  mg_job<false, double>(S, S.job[blockIdx.x], sh, [&](int i, double v, double) {
     if (LAST) G(out)[o + i] = scale * v + (add ? G(add)[o + i] : 0.0);
     else G(S.y)[i] = v;
   });
@@ -236,7 +270,10 @@ void mg_cycle(hipStream_t s, const MGroup* groups, int nvec, const int* nblocks,
 template <int KIND, class VT>
 static void mg_launch(hipStream_t s, const KLaunch& L, const MLaunch& M, int slot, int par) {
   if (M.nblocks[slot] == 0) return;
-  if (L.ngroups == 1 && M.one.part_z)
+  if (KIND == 2 && L.ngroups == 1 && M.one.st[slot].val2)
+    hipLaunchKernelGGL((k_mg1<3, VT>), dim3(M.nblocks[slot]), dim3(KBS), 0, s, M.kone, M.one,
+                       M.one.st[slot], par);
+  else if (L.ngroups == 1 && M.one.part_z)
     hipLaunchKernelGGL((k_mg1<KIND, VT>), dim3(M.nblocks[slot]), dim3(KBS), 0, s, M.kone, M.one,
                        M.one.st[slot], par);
   else

@@ -109,6 +109,7 @@ struct MgProduct {
   std::vector<int32_t> rp;
   RawVec<int32_t> col;
   RawVec<double> val;
+  RawVec<double> val2;            // last product with w = A z beside z: A times val (or empty)
   std::vector<MgJob> jobs;
 };
 

@@ -299,7 +299,7 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
   auto iterate = [&](int par) {
     if (mg) {
       mg_apply(s, S.L, S.M, par);
-      pcg_spmv_only(s, S.L);
+      if (!S.M.with_w) pcg_spmv_only(s, S.L);
       mg_update(s, S.L, S.M, par);
     } else if (fused) {
       T.run(s, S.kid[0], [&] { fcg_iter(s, S.F, par); });
@@ -645,7 +645,7 @@ void Run::upload_multigrid() {
                           stream));
     HIP_OK(hipMemcpyAsync(mg_jobs[k], p.jobs.data(), sizeof(MgJob) * p.jobs.size(),
                           hipMemcpyHostToDevice, stream));
-    if (mixed) {
+    if (mixed && !p.val2.size()) {
       std::vector<float> f(nnz);
       for (size_t q = 0; q < nnz; ++q) f[q] = (float)p.val[q];
       HIP_OK(hipMemcpyAsync(mg_val[k], f.data(), sizeof(float) * nnz, hipMemcpyHostToDevice,
@@ -658,6 +658,11 @@ void Run::upload_multigrid() {
     g.st[k].rp = mg_rp[k];
     g.st[k].col = mg_col[k];
     g.st[k].val = mg_val[k];
+    if (p.val2.size()) {
+      HIP_OK(hipMemcpyAsync(mg_val2, p.val2.data(), sizeof(double) * nnz, hipMemcpyHostToDevice,
+                            stream));
+      g.st[k].val2 = mg_val2;
+    }
     g.st[k].job = mg_jobs[k];
   }
   // inputs and outputs (mesh.hpp, MgHierarchy)
@@ -675,6 +680,7 @@ void Run::upload_multigrid() {
   g.nz = (int32_t)h.st[MG_SLOTS - 1].jobs.size();
   set_p.M.groups = mgroup;
   set_p.M.fp32 = mixed ? 1 : 0;
+  set_p.M.with_w = g.st[MG_SLOTS - 1].val2 ? 1 : 0;
   set_p.M.one = g;
   set_p.M.kone = set_p.h_groups[0];
   set_p.h_mgroups = {g};
@@ -805,13 +811,14 @@ void Run::layout(Carver& c) {
       if (p.jobs.empty()) continue;
       mg_rp[k] = c.take<int32_t>(p.n + 1);
       mg_col[k] = c.take<int32_t>((int64_t)p.col.size());
-      mg_val[k] = c.take<char>((int64_t)p.val.size() * vsz);
+      mg_val[k] = c.take<char>((int64_t)p.val.size() * (p.val2.size() ? 8 : vsz));
       mg_jobs[k] = c.take<MgJob>((int64_t)p.jobs.size());
     }
     mg_buf[0] = c.take<double>(n1 + (mgh->base ? mgh->nbase : mgh->below));
     mg_buf[1] = c.take<double>(mgh->base ? mgh->nbase + mgh->below : 1);
     mg_buf[2] = c.take<double>(mgh->below);
-    mg_part = c.take<double>((int64_t)mgh->st[MG_SLOTS - 1].jobs.size());
+    mg_part = c.take<double>(2 * (int64_t)mgh->st[MG_SLOTS - 1].jobs.size());
+    mg_val2 = c.take<double>((int64_t)mgh->st[MG_SLOTS - 1].val2.size());
     mgroup = c.take<MGroup>(1);
   }
   spart = c.take<double>(8192 * 2);

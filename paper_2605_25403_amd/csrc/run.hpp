@@ -245,6 +245,7 @@ struct Run {
   MgJob* mg_jobs[MG_SLOTS] = {};
   double* mg_buf[3] = {};      // [r_0 | e ..], [r_1 | e ..], [r ..] (mesh.hpp)
   double* mg_part = nullptr;
+  double* mg_val2 = nullptr;             // second values of the last product
   int mom_it = 0;              // this step's momentum iterations (most of any component)
   MGroup* mgroup = nullptr;
   double* spart = nullptr;    // scratch partials for one-off reductions [8192*2]

@@ -355,7 +355,7 @@ void Steady::upload_multigrid() {
       double *a = mg_buf[0] + c * la, *b = mg_buf[1] + c * lb, *r = mg_buf[2] + c * h.below;
       const double* xs[MG_SLOTS] = {a, b, r, b, a};
       double* ys[MG_SLOTS] = {two ? b : r, r, two ? b + h.nbase : a + n2, a + n2, nullptr};
-      g[c].st[k] = MgStep{mg_rp[k], mg_col[k], mg_val[k], mg_jobs[k], xs[k], ys[k],
+      g[c].st[k] = MgStep{mg_rp[k], mg_col[k], mg_val[k], nullptr, mg_jobs[k], xs[k], ys[k],
                           (int32_t)p.jobs.size(), 0};
     }
   }

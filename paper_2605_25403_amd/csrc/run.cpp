@@ -250,7 +250,7 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
   // is a packet of its own on the stream)
   Pace& pace = S.now();
   const bool measure = time_bursts && (pace.us_per_launch == 0.0 || pace.us_per_poll == 0.0 ||
-                                       pace.solves % 16 == 0);
+                                       pace.solves < 3 || pace.solves % 16 == 0);
   ++pace.solves;
   hipEvent_t* ev = measure ? chunk_events(2 * kChunkEvents) : nullptr;
   int nburst = 0, timed_launches = 0;
@@ -439,7 +439,7 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
                                    expect <= kWholeChunk))) {
         // one more: a converged system's check is the next iteration's first
         // kernel, and the rest of that iteration only reads the status
-        chunk = std::max(least, expect + 1);
+        chunk = expect + 1;
       } else if (restarted || launched >= S.now().last_iters) {
         chunk = least << std::min(tail, 10);
         ++tail;
@@ -532,8 +532,12 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
     }
     S.now().us_per_poll = 1000.0 * gaps / after_poll.size();
   }
+  // the fused form's finish copies x back; the others' zeroes the x of systems
+  // whose right-hand side is zero
+  bool zero = false;
+  each([&](const KState& k) { zero |= k.status == KS_ZERO; });
   if (fused) fcg_finish(s, S.F);
-  else ksys_finish(s, S.L);
+  else if (zero) ksys_finish(s, S.L);
   return result();
 }
 

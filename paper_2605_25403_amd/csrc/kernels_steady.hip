@@ -123,6 +123,52 @@ k_maxpy(int64_t n, const double* V, int64_t ldv, const double* h, int k, double 
   y[i] += sign * s;
 }
 
+// One Gram-Schmidt pass from the partial sums of k_mdot (nblk per vector):
+// h[j] = their sum, y -= sum_{j<k} h[j] V[j]; block 0 keeps h in out. nrm (may
+// be null) receives the block's partial sum of y^2. Every block adds the
+// partials up by itself, a thread per vector: a launch of its own for that
+// costs more (48^2 squares: 11 partials of up to 61 vectors).
+__global__ void __launch_bounds__(SBS)
+k_gs_pass(int64_t n, const double* V, int64_t ldv, const double* part, int nblk, int k, double* out,
+          double* y, double* nrm) {
+  __shared__ double h[512], sh[SBS / 64];
+  for (int j = threadIdx.x; j < k; j += SBS) {
+    double s = 0.0;
+    for (int b = 0; b < nblk; ++b) s += part[(int64_t)j * nblk + b];
+    h[j] = s;
+    if (blockIdx.x == 0) out[j] = s;
+  }
+  __syncthreads();
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  double yi = 0.0;
+  if (i < n) {
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    int j = 0;
+    for (; j + 4 <= k; j += 4)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q] += h[j + q] * V[(int64_t)(j + q) * ldv + i];
+    for (; j < k; ++j) s[0] += h[j] * V[(int64_t)j * ldv + i];
+    yi = y[i] - ((s[0] + s[1]) + (s[2] + s[3]));
+    y[i] = yi;
+  }
+  if (nrm) {
+    const double q = block_sum(yi * yi, sh);
+    if (threadIdx.x == 0) nrm[blockIdx.x] = q;
+  }
+}
+
+// y /= ||y||, ||y||^2 from nblk partial sums (block 0 keeps it in out)
+__global__ void __launch_bounds__(SBS)
+k_gs_scale(int64_t n, const double* nrm, int nblk, double* out, double* y) {
+  __shared__ double sh[SBS / 64];
+  double q = 0.0;
+  for (int b = threadIdx.x; b < nblk; b += SBS) q += nrm[b];
+  q = block_sum(q, sh);
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) out[0] = q;
+  if (i < n) y[i] = q > 0.0 ? y[i] / sqrt(q) : 0.0;
+}
+
 // y = x / sqrt(*nrm2)
 __global__ void __launch_bounds__(SBS)
 k_scale_inv_norm(int64_t n, const double* x, const double* nrm2, double* y) {
@@ -296,6 +342,20 @@ void maxpy(hipStream_t s, int64_t n, const double* V, int64_t ldv, const double*
            double sign, double* y) {
   if (k <= 0 || n <= 0) return;
   launch(k_maxpy, dim3(grid(n)), dim3(SBS), 0, s, n, V, ldv, h, k, sign, y);
+}
+
+bool orthonormalize(hipStream_t s, int64_t n, const double* V, int k, double* part, double* h1,
+                    double* h2, double* nrm2, double* w) {
+  const int nb = mdot_blocks(n), ng = (int)grid(n);
+  if (n <= 0 || k <= 0 || k > 512 || nb > kGsParts) return false;
+  double* nrm = part + (int64_t)k * nb;
+  launch(k_mdot, dim3(nb, k), dim3(SBS), 0, s, n, V, n, (const double*)w, k, part, nb);
+  launch(k_gs_pass, dim3(ng), dim3(SBS), 0, s, n, V, n, (const double*)part, nb, k, h1, w,
+         (double*)nullptr);
+  launch(k_mdot, dim3(nb, k), dim3(SBS), 0, s, n, V, n, (const double*)w, k, part, nb);
+  launch(k_gs_pass, dim3(ng), dim3(SBS), 0, s, n, V, n, (const double*)part, nb, k, h2, w, nrm);
+  launch(k_gs_scale, dim3(ng), dim3(SBS), 0, s, n, (const double*)nrm, ng, nrm2, w);
+  return true;
 }
 
 void scale_inv_norm(hipStream_t s, int64_t n, const double* x, const double* nrm2, double* y) {

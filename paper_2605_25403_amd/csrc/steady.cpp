@@ -130,7 +130,7 @@ void Steady::layout(Carver& c) {
   V = c.take<double>((int64_t)(m + 1) * n);
   Z = c.take<double>((int64_t)m * n);
   h = c.take<double>(2 * (m + 2));
-  part = c.take<double>((int64_t)(m + 2) * mdot_blocks(n));
+  part = c.take<double>((int64_t)(m + 10) * mdot_blocks(n));
   scal = c.take<double>(16);
   kva = c.take<double>(8 * nu_rows);
   ib = c.take<double>(nu_rows);
@@ -318,7 +318,7 @@ constexpr int kPollEvery = 4;   // multigrid FGMRES iterations between two polls
 // least reduction of the residual by a multigrid FGMRES cycle (the first one is
 // measured against the start as well): a cycle of 60 iterations reaches 1e-12
 // where viscosity dominates and gains some 300 on 24^2 squares at nu = 0.003
-// (1132 iterations in all, 124 ms against 701 ms with inner solves); below 30 the
+// (1132 iterations in all, 106 ms against 701 ms with inner solves); below 30 the
 // eight or more cycles that 1e-12 takes near the cost of the inner solves
 constexpr double kCycleGain = 30.0;
 
@@ -411,12 +411,14 @@ bool Steady::solve_multigrid(double beta0, int& total) {
       mg_cycle(s, mg_groups, dim, mg_nblocks, 1.0 / sp.nu, ix, zk, n2);
       // w = J z_k, orthogonalized twice against v_0..v_k (classical Gram-Schmidt)
       sell_axpby(s, n, j_sp, j_col, Jv, zk, 1.0, 0.0, nullptr, w);
-      mdot(s, n, V, n, w, k + 1, part, hc, 0);
-      maxpy(s, n, V, n, hc, k + 1, -1.0, w);
-      mdot(s, n, V, n, w, k + 1, part, hc + M, 0);
-      maxpy(s, n, V, n, hc + M, k + 1, -1.0, w);
-      mdot(s, n, w, n, w, 1, part, hc + 2 * M, 0);
-      scale_inv_norm(s, n, w, hc + 2 * M, w);
+      if (!orthonormalize(s, n, V, k + 1, part, hc, hc + M, hc + 2 * M, w)) {
+        mdot(s, n, V, n, w, k + 1, part, hc, 0);
+        maxpy(s, n, V, n, hc, k + 1, -1.0, w);
+        mdot(s, n, V, n, w, k + 1, part, hc + M, 0);
+        maxpy(s, n, V, n, hc + M, k + 1, -1.0, w);
+        mdot(s, n, w, n, w, 1, part, hc + 2 * M, 0);
+        scale_inv_norm(s, n, w, hc + 2 * M, w);
+      }
       ++k;
       ++total;
       // the columns come back a few iterations at a time: a poll costs a

@@ -15,10 +15,10 @@
 // (amg.hpp), Mp by three Chebyshev steps on its consistent form: a fixed
 // preconditioner of some twenty launches, which takes 50 to 100 iterations
 // whatever the mesh where viscosity dominates: 48^2 squares at nu = 1 took 303
-// iterations with 11898 inner ones in 387 ms, and take 188 in 25 ms (130 us an
-// iteration, the chain of launches); 8^3 cubes 639 and 150 ms. Where an FGMRES
-// cycle gains less than a factor 30 (20^2 squares at nu = 0.02: 868 ms before,
-// 794 ms now with the cycle tried first; nu = 0.005: 6127 and 6017 ms), the Newton system is solved again with A by a
+// iterations with 11898 inner ones in 387 ms, and take 188 in 22 ms (115 us an
+// iteration, the chain of launches); 8^3 cubes 639 and 142 ms. Where an FGMRES
+// cycle gains less than a factor 30 (20^2 squares at nu = 0.02: 870 ms before,
+// 770 ms now with the cycle tried first; nu = 0.005: 6130 and 6120 ms), the Newton system is solved again with A by a
 // loose inner Jacobi-BiCGStab solve and S = (1/nu) diag(Mp 1). The pressure is
 // shifted to zero integral mean after every step.
 #pragma once
@@ -66,6 +66,14 @@ void mdot(hipStream_t s, int64_t n, const double* V, int64_t ldv, const double* 
 void maxpy(hipStream_t s, int64_t n, const double* V, int64_t ldv, const double* h, int k,
            double sign, double* y);
 void scale_inv_norm(hipStream_t s, int64_t n, const double* x, const double* nrm2, double* y);
+// Two classical Gram-Schmidt passes of w against V[0..k) and its normalization
+// in five launches (nine one by one: 48^2 squares 25.4 ms a solve for 22); h1,
+// h2: the passes' coefficients, nrm2: ||w||^2 before the scaling; part holds
+// (k + 8) * mdot_blocks(n). False, and nothing done, past
+// kGsParts partial sums per vector: each of its blocks adds all of them up.
+constexpr int kGsParts = 64;
+bool orthonormalize(hipStream_t s, int64_t n, const double* V, int k, double* part, double* h1,
+                    double* h2, double* nrm2, double* w);
 void prec_pressure(hipStream_t s, int64_t n1, const double* vp, const double* w, double nu,
                    double* zp);
 // out = scale M^{-1} v to the accuracy of three Chebyshev steps (M the P1 mass

@@ -48,3 +48,21 @@ def test_polynomial_state(dim, n, nu):
     print(st, flush=True)
     assert np.abs(s.velocity() - pb.u(S.xu, 0.0).T).max() <= 1e-11
     assert np.abs(s.pressure() - pb.p(S.xp, 0.0)).max() <= 1e-10
+
+
+def test_long_vectors_are_orthonormalized_by_the_general_kernels():
+    """More rows than the five-launch Gram-Schmidt takes (131072), and the
+    largest mesh below: the polynomial state to ten times the relative change
+    at which the iteration stops (1e-10)."""
+    torch, I = require_gpu()
+    for n in (120, 122):
+        print(f"steady multigrid n={n}", flush=True)
+        s = I.Steady(I.Mesh.unit_square(n), nu=1.0)
+        s.set_builtin(I.IPCS_SOL_POLY_STEADY_2D)
+        st = s.solve()
+        S = fem.Space(*mesh.unit_square(n, n))
+        assert (2 * len(S.xu) + len(S.xp) > 131072) == (n == 122)
+        pb = problems.PolySteady2D(1.0)
+        u, p = pb.u(S.xu, 0.0).T, pb.p(S.xp, 0.0)
+        print(rel(s.velocity(), u), rel(s.pressure(), p), st, flush=True)
+        assert rel(s.velocity(), u) <= 1e-9 and rel(s.pressure(), p) <= 1e-9

@@ -327,6 +327,19 @@ struct Level {
   double omega = 0.0;
 };
 
+// f(q, p) for every entry p of Sub, q the entry of Big at its place (the pattern
+// of Big holds Sub's); rows in parallel.
+template <class F>
+void each_match(const Csr& Big, const Csr& Sub, F f) {
+  ranges(Big.n, [&](int, int64_t lo, int64_t hi) {
+    std::vector<int32_t> at(Big.m, 0);
+    for (int64_t i = lo; i < hi; ++i) {
+      for (int32_t q = Big.rp[i]; q < Big.rp[i + 1]; ++q) at[Big.col[q]] = q;
+      for (int32_t p = Sub.rp[i]; p < Sub.rp[i + 1]; ++p) f(at[Sub.col[p]], p);
+    }
+  });
+}
+
 // X = P - w D^{-1} (A P), s = -w D^{-1}: the pattern of A P holds P's
 inline Csr smoothed(const Csr& P, const Csr& AP, const std::vector<double>& s) {
   Csr Q;
@@ -338,13 +351,11 @@ inline Csr smoothed(const Csr& P, const Csr& AP, const std::vector<double>& s) {
   ranges(Q.n, [&](int, int64_t lo, int64_t hi) {
     for (int64_t i = lo; i < hi; ++i)
       for (int32_t q = AP.rp[i]; q < AP.rp[i + 1]; ++q) {
-        double v = s[i] * AP.val[q];
-        for (int32_t p = P.rp[i]; p < P.rp[i + 1]; ++p)
-          if (P.col[p] == AP.col[q]) v += P.val[p];
         Q.col[q] = AP.col[q];
-        Q.val[q] = v;
+        Q.val[q] = s[i] * AP.val[q];
       }
   });
+  each_match(Q, P, [&](int32_t q, int32_t p) { Q.val[q] += P.val[p]; });
   return Q;
 }
 
@@ -428,12 +439,7 @@ inline Csr smoother(const Level& L, int m) {
   const Csr ASX = product(A, SX);
   if (ASX.n == 0) return Csr{};
   Csr Y = smoothed(SX, ASX, sc);           // its pattern holds X's
-  ranges(A.n, [&](int, int64_t lo, int64_t hi) {
-    for (int64_t i = lo; i < hi; ++i)
-      for (int32_t q = Y.rp[i]; q < Y.rp[i + 1]; ++q)
-        for (int32_t p = X.rp[i]; p < X.rp[i + 1]; ++p)
-          if (X.col[p] == Y.col[q]) Y.val[q] += X.val[p];
-  });
+  each_match(Y, X, [&](int32_t q, int32_t p) { Y.val[q] += X.val[p]; });
   return Y;
 }
 
@@ -807,14 +813,8 @@ inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0, bool singular) {
     if (W.n != 0 && W.nnz() <= kWithW) {
       RawVec<double> z;
       z.alloc(W.nnz());
-      ranges(W.n, [&](int, int64_t lo, int64_t hi) {
-        for (int64_t i = lo; i < hi; ++i)
-          for (int32_t q = W.rp[i]; q < W.rp[i + 1]; ++q) {
-            z[q] = 0.0;
-            for (int32_t p = up.rp[i]; p < up.rp[i + 1]; ++p)
-              if (up.col[p] == W.col[q]) z[q] = up.val[p];
-          }
-      });
+      std::fill(z.data(), z.data() + z.size(), 0.0);
+      each_match(W, up, [&](int32_t q, int32_t p) { z[q] = up.val[p]; });
       h->st[4].val2 = std::move(W.val);
       W.val = std::move(z);
       up = std::move(W);

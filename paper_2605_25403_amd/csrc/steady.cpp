@@ -314,11 +314,16 @@ void Steady::to_run() {
 
 namespace {
 
-constexpr int kPollEvery = 4;   // multigrid FGMRES iterations between two polls
+// Multigrid FGMRES iterations before the first poll of a cycle; then half of what
+// the residual's mean rate so far leaves to do, at least two. A poll costs 25 us,
+// an iteration past the end 115 us, and the rate rises towards the end (polls
+// every four iterations took 33^2 squares 20.8 ms for 18.8, 24^2 at nu = 0.003
+// 105 for 96).
+constexpr int kFirstPoll = 4;
 // least reduction of the residual by a multigrid FGMRES cycle (the first one is
 // measured against the start as well): a cycle of 60 iterations reaches 1e-12
 // where viscosity dominates and gains some 300 on 24^2 squares at nu = 0.003
-// (1132 iterations in all, 106 ms against 701 ms with inner solves); below 30 the
+// (1152 iterations in all, 96 ms against 701 ms with inner solves); below 30 the
 // eight or more cycles that 1e-12 takes near the cost of the inner solves
 constexpr double kCycleGain = 30.0;
 
@@ -396,7 +401,7 @@ bool Steady::solve_multigrid(double beta0, int& total) {
     std::fill(H.begin(), H.end(), 0.0);
     std::fill(g.begin(), g.end(), 0.0);
     g[0] = beta;
-    int k = 0, seen = 0;
+    int k = 0, seen = 0, every = kFirstPoll;
     bool done = false;
     while (k < M && total < most && !done) {
       double* vk = V + (size_t)k * n;
@@ -421,9 +426,8 @@ bool Steady::solve_multigrid(double beta0, int& total) {
       }
       ++k;
       ++total;
-      // the columns come back a few iterations at a time: a poll costs a
-      // quarter of an iteration
-      if (k < M && total < most && k - seen < kPollEvery) continue;
+      // the columns come back several iterations at a time
+      if (k < M && total < most && k - seen < every) continue;
       fetch(s, hcol + (size_t)seen * ldh, hb.data() + (size_t)seen * ldh, (k - seen) * ldh);
       for (int j = seen; j < k && !done; ++j) {
         const double* hj = hb.data() + (size_t)j * ldh;
@@ -447,6 +451,10 @@ bool Steady::solve_multigrid(double beta0, int& total) {
         }
       }
       seen = k;
+      const double left = std::fabs(g[k]) / (sp.lin_tol * beta0), rate = std::fabs(g[k]) / beta;
+      every = rate < 1.0 && left > 1.0
+                  ? std::max(2, (int)std::min(0.5 * k * std::log(left) / -std::log(rate), 64.0))
+                  : kFirstPoll;
     }
     std::vector<double> y(k, 0.0);
     for (int i = k - 1; i >= 0; --i) {

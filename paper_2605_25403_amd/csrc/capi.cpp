@@ -113,32 +113,26 @@ void read_back(hipStream_t s, const double* src, int64_t n, F put) {
   struct Lease {
     hipStream_t s;
     double* p = ipcs::staging_take();
-    hipEvent_t ev[2] = {};
     bool sent = false;
     explicit Lease(hipStream_t st) : s(st) {}
     ~Lease() {
       if (sent) (void)hipStreamSynchronize(s);   // no copy outlives the lease
-      for (hipEvent_t e : ev)
-        if (e) (void)hipEventDestroy(e);
       ipcs::staging_give(p);
     }
   } b(s);
   constexpr int64_t H = ipcs::kStagingHalf;
+  const int64_t chunks = (n + H - 1) / H;
   auto copy = [&](int64_t c) {
     const int64_t a = c * H, k = std::min(H, n - a);
     b.sent = true;
     HIP_OK(hipMemcpyAsync(b.p + (c & 1) * H, src + a, sizeof(double) * k, hipMemcpyDeviceToHost,
                           s));
-    if (n > H) HIP_OK(hipEventRecord(b.ev[c & 1], s));
   };
-  if (n > H)
-    for (hipEvent_t& e : b.ev) HIP_OK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-  const int64_t chunks = (n + H - 1) / H;
   if (chunks > 0) copy(0);
   for (int64_t c = 0; c < chunks; ++c) {
+    HIP_OK(hipStreamSynchronize(s));   // chunk c is here
+    b.sent = false;
     if (c + 1 < chunks) copy(c + 1);
-    if (n > H) HIP_OK(hipEventSynchronize(b.ev[c & 1]));
-    else HIP_OK(hipStreamSynchronize(s));
     const int64_t a = c * H, k = std::min(H, n - a);
     const double* h = b.p + (c & 1) * H;
     constexpr int64_t kPiece = 16384;

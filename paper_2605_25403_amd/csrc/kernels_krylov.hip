@@ -64,8 +64,12 @@ namespace ipcs {
 
 // Row i of the group's SELL-64 matrix applied to NS gathered vectors:
 // acc[j] = sum_k A(i, col_k) * x_j(col_k), in FP64 whatever the stored value
-// type VT; gath(c, x) loads row c of every vector. The slice width is uniform in the wavefront; the last chunk
-// of eight re-reads entry w-1 and discards it.
+// type VT; gath(c, x) loads row c of every vector. The slice width is uniform in
+// the wavefront; the last chunk of eight re-reads entry w-1 and discards it.
+// Bound by the matrix's bytes (512^2 squares: 195 MB with the vectors in 35 to
+// 39 us, 95 % of a copy's rate) and, on tetrahedra, by the lines the gathers
+// touch (20 per wave and column: 218 us at 64^3 with FP32 values, 240 before the
+// systems' entries came by one wide load).
 template <int NS, class VT, class GF>
 __device__ __forceinline__ void sell_row(const KGroup& g, int i, GF gath, double (&acc)[NS]) {
   const gptr<const VT> val = G(static_cast<const VT*>(g.val));

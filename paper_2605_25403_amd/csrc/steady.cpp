@@ -382,7 +382,9 @@ bool Steady::solve_multigrid(double beta0, int& total) {
   double beta = beta0, rr = 0.0;
   total = 0;
   const int most = sp.lin_maxit;
-  double last = beta0 * kCycleGain;
+  double last = beta0 * kCycleGain, best = 0.0;
+  int stalls = 0;
+  bool done = false;   // the recursive residual of the last cycle met the tolerance
   while (total < most) {
     if (total == 0) {
       copy_vec(s, n, R, V);
@@ -392,8 +394,18 @@ bool Steady::solve_multigrid(double beta0, int& total) {
       fetch(s, scal + 1, &rr, 1);
       beta = std::sqrt(rr);
       if (beta <= sp.lin_tol * beta0) return true;
-      // a cycle that gains too little: viscosity does not dominate
-      if (!(beta * kCycleGain <= last)) return false;
+      if (done) {
+        // the true residual did not: the next cycle starts from it, until such
+        // checks stall as the other solves' do
+        if (best == 0.0 || beta <= 0.9 * best) {
+          best = beta;
+          stalls = 0;
+        } else if (++stalls >= KSTALL_CHECKS) {
+          return false;
+        }
+      } else if (!(beta * kCycleGain <= last)) {
+        return false;   // a cycle that gains too little: viscosity does not dominate
+      }
       last = beta;
     }
     mdot(s, n, V, n, V, 1, part, scal + 2, 0);
@@ -402,7 +414,7 @@ bool Steady::solve_multigrid(double beta0, int& total) {
     std::fill(g.begin(), g.end(), 0.0);
     g[0] = beta;
     int k = 0, seen = 0, every = kFirstPoll;
-    bool done = false;
+    done = false;
     while (k < M && total < most && !done) {
       double* vk = V + (size_t)k * n;
       double* zk = Z + (size_t)k * n;
@@ -466,12 +478,12 @@ bool Steady::solve_multigrid(double beta0, int& total) {
     maxpy(s, n, Z, n, h, k, 1.0, dx);
     HIP_OK(hipStreamSynchronize(s));   // y is a host vector about to go away
     if (done) {
-      // the recursive residual is there: so must the true one be, else the next
-      // cycle starts from it
+      // the recursive residual is there: so must the true one be
       sell_axpby(s, n, j_sp, j_col, Jv, dx, -1.0, 1.0, R, tmp);
       mdot(s, n, tmp, n, tmp, 1, part, scal + 1, 0);
       fetch(s, scal + 1, &rr, 1);
-      if (std::isfinite(rr) && std::sqrt(rr) <= 2.0 * sp.lin_tol * beta0) return true;
+      if (!std::isfinite(rr)) return false;
+      if (std::sqrt(rr) <= sp.lin_tol * beta0) return true;
     }
   }
   return false;

@@ -321,10 +321,13 @@ namespace {
 // 105 for 96).
 constexpr int kFirstPoll = 4;
 // least reduction of the residual by a multigrid FGMRES cycle (the first one is
-// measured against the start as well): a cycle of 60 iterations reaches 1e-12
-// where viscosity dominates and gains some 300 on 24^2 squares at nu = 0.003
-// (1152 iterations in all, 96 ms against 701 ms with inner solves); below 30 the
-// eight or more cycles that 1e-12 takes near the cost of the inner solves
+// measured against the start): a cycle of 60 iterations reaches 1e-12 where
+// viscosity dominates; on 24^2 squares at nu = 0.003 the first gains 280 and more
+// and the following ones 68 to 210 (1152 iterations in all, 96 ms against 701 ms
+// with inner solves); below 30 the eight or more cycles that 1e-12 takes near the
+// cost of the inner solves. Where the first one gains less (7 on 24^2 at nu =
+// 0.002, 2 to 5 on 20^2 at 0.02 and 0.01), none of the following ones gained more
+// than 12, so one cycle decides.
 constexpr double kCycleGain = 30.0;
 
 // host copy of n doubles from the device (synchronizes the stream)
@@ -382,7 +385,7 @@ bool Steady::solve_multigrid(double beta0, int& total) {
   double beta = beta0, rr = 0.0;
   total = 0;
   const int most = sp.lin_maxit;
-  double last = beta0 * kCycleGain, best = 0.0;
+  double last = beta0, best = 0.0;
   int stalls = 0;
   bool done = false;   // the recursive residual of the last cycle met the tolerance
   while (total < most) {

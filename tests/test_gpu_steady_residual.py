@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 
 from oracle import fem, mesh, problems, steady
-from tests.gpu_common import require_gpu
+from tests.gpu_common import rel, require_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +44,31 @@ def test_true_residual_meets_the_tolerance(n, restart, lin_tol):
                 for v in ((R - J @ dx - exact).astype(float), (other - J) @ dx)]
     print(f"  residual {res:.3e} roundings {rounding}", st, flush=True)
     assert res <= lin_tol + sum(rounding)
+
+
+def test_one_cycle_decides_for_the_inner_solves():
+    """Convection dominates on 24^2 squares at nu = 0.002 from the second Newton
+    step on: the inner solves give the oracle's fields (1e-10, as the steady
+    solver's other tests), after a single multigrid cycle that gains too little.
+    A linear iteration cap between one cycle and two shows the cycles: it ends the
+    inner solves too, and the count that is left is the multigrid one."""
+    torch, I = require_gpu()
+    print("steady: fallback to the inner solves", flush=True)
+    n, nu, restart, cap = 24, 0.002, 60, 100
+    m = I.Mesh.unit_square(n)
+    o = steady.SteadyNewton(fem.Space(*mesh.unit_square(n, n)), problems.SteadyPaper2D(nu), nu)
+    o.run()
+    s = I.Steady(m, nu=nu, restart=restart)
+    s.set_builtin(I.IPCS_SOL_STEADY_PAPER_2D)
+    st = s.solve()
+    errs = [rel(s.velocity()[c], o.U[c]) for c in range(2)] + [rel(s.pressure(), o.P)]
+    print(" ", errs, st, flush=True)
+    assert st["inner_it"] > 0 and max(errs) <= 1e-10
+    s = I.Steady(m, nu=nu, restart=restart, lin_maxit=cap)
+    s.set_builtin(I.IPCS_SOL_STEADY_PAPER_2D)
+    s.step()
+    with pytest.raises(I.IpcsError) as e:
+        s.solve()
+    print(" ", e.value.stats, flush=True)
+    assert e.value.code == I.IPCS_E_NOT_CONVERGED
+    assert e.value.stats["lin_it"] == restart

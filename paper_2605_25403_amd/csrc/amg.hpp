@@ -445,9 +445,11 @@ inline Csr smoother(const Level& L, int m) {
 
 // Blocks of a product: rows in runs of about kMgEntries entries, each run with
 // one number of lanes per row (a power of two from the rows' mean length).
-// Segments (levels) of very different row lengths are cut apart.
+// Segments (levels) of very different row lengths are cut apart. At most `most`
+// blocks (0: any number): the runs grow until they fit.
 constexpr int64_t kMgEntries = 1400;
-inline void make_jobs(const Csr& X, const std::vector<int64_t>& segs, std::vector<MgJob>& jobs) {
+inline void make_jobs(const Csr& X, const std::vector<int64_t>& segs, std::vector<MgJob>& jobs,
+                      int64_t most = 0, int64_t entries = kMgEntries) {
   jobs.clear();
   for (size_t s = 0; s + 1 < segs.size(); ++s) {
     const int64_t lo = segs[s], hi = segs[s + 1];
@@ -457,10 +459,12 @@ inline void make_jobs(const Csr& X, const std::vector<int64_t>& segs, std::vecto
     while (lg < 8 && (4 << lg) < mean) ++lg;
     if (lg == 7) lg = 8;                     // one row per wavefront or per block
     const int64_t per = 256 >> lg;           // rows a block takes at once
-    const int64_t reps = std::max<int64_t>(1, (int64_t)(kMgEntries / std::max(1.0, mean * per)));
+    const int64_t reps = std::max<int64_t>(1, (int64_t)(entries / std::max(1.0, mean * per)));
     for (int64_t r = lo; r < hi; r += per * reps)
       jobs.push_back(MgJob{(int32_t)r, (int32_t)std::min(hi, r + per * reps), lg, 0});
   }
+  if (most > 0 && (int64_t)jobs.size() > most && entries < X.nnz())
+    return make_jobs(X, segs, jobs, most, 2 * entries);
   // runs of 8 consecutive blocks per XCD (blocks are dealt to the 8 XCDs in
   // turn): neighbouring rows gather neighbouring entries through one L2
   constexpr int64_t kXcd = 8, kRun = 8, span = kXcd * kRun;
@@ -798,7 +802,7 @@ inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0, bool singular) {
   auto put = [&](int slot, Csr& X, const std::vector<int64_t>& s) {
     MgProduct& p = h->st[slot];
     p.n = X.n;
-    make_jobs(X, s, p.jobs);
+    make_jobs(X, s, p.jobs, slot == MG_SLOTS - 1 ? MG_LAST_JOBS : 0);
     p.rp = std::move(X.rp);
     p.col = std::move(X.col);
     p.val = std::move(X.val);

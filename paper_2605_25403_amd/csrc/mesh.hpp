@@ -122,6 +122,10 @@ struct MgProduct {
 //   3:                                                  e_1 from [r_1; e_2; ..; e_L]
 //   4: base 0: z from [r_0; e_1; ..; e_L]       base 1: z from [r_0; e_1]
 constexpr int MG_SLOTS = 5;
+// Most blocks of the last product: each writes partial sums that every block of
+// the vector update adds up (KNB_MAX of the Krylov kernels). Squares reach it at
+// 1024^2, cubes at 80^3.
+constexpr int MG_LAST_JOBS = 8192;
 struct MgHierarchy {
   int64_t n = 0;                  // unknowns of the finest level
   int levels = 0, base = 0;

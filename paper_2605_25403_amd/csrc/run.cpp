@@ -625,14 +625,13 @@ void Run::choose_poisson_form() {
 // block's 2,048 short rows and kMgRows the one-launch-per-iteration form stays,
 // at most 170 iterations, whose counts its two-kernel twin reproduces.
 constexpr int64_t kMgRows = 2560, kMgWide = 500;
+static_assert(MG_LAST_JOBS == KNB_MAX, "partial sums of a multigrid product");
 void Run::choose_preconditioner() {
   mgh.reset();
   if (prm.poisson_part_rows != 0 || prm.poisson_s != 0) return;
   if (n1 <= (mesh->e11.maxw <= 8 ? kMgRows : kMgWide)) return;
   if (small_form(n1, mesh->e11.maxw, mesh->e11.nent, true, false).width) return;
   mgh = mesh->multigrid();
-  // the update's blocks re-read one partial sum per block of the last product
-  if (mgh && (int64_t)mgh->st[MG_SLOTS - 1].jobs.size() > KNB_MAX) mgh.reset();
 }
 
 void Run::upload_multigrid() {

@@ -1,0 +1,40 @@
+"""The multigrid hierarchy's host code (amg.hpp) on the CPU, through
+tests/host_multigrid.cpp built with g++."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2605_25403_amd", "csrc")
+UNITS = ["mesh.cpp", "parts.cpp", "rules.cpp"]
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+
+
+def build(exe, flags):
+    cmd = ["g++", "-std=c++17", "-fopenmp", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I",
+           os.path.join(ROOT, "include"), "-I", CSRC] + flags
+    cmd += [os.path.join(ROOT, "tests", "host_multigrid.cpp")]
+    cmd += [os.path.join(CSRC, u) for u in UNITS] + ["-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-4000:]
+    return exe
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    return build(str(tmp_path_factory.mktemp("mg") / "host_multigrid"), ["-O2"])
+
+
+def run(exe, what):
+    r = subprocess.run([exe, what], capture_output=True, text=True, timeout=600,
+                       env=dict(os.environ, OMP_NUM_THREADS="4"))
+    assert r.returncode == 0 and "ok" in r.stdout, (r.returncode, r.stdout[-2000:],
+                                                    r.stderr[-4000:])
+
+
+def test_the_last_product_fits_the_partial_sums_of_large_meshes(program):
+    """1024^2 squares and 80^3 cubes are past 8192 blocks of the usual size."""
+    run(program, "large")

@@ -273,7 +273,12 @@ void solve_shared(const std::vector<Run*>& runs, int which, KMethod m, hipStream
         if (code == IPCS_OK && c != IPCS_OK) code = c;
       }
       rc[r] = code;
-      if (sh.S.mg && code != IPCS_OK) again.push_back(r);
+      if (sh.S.mg && code != IPCS_OK) {   // repeated by the Jacobi form (Run::poisson_cg)
+        r->prepare_jacobi(mine[0]);
+        again.push_back(r);
+        continue;
+      }
+      if (which == 1) r->count_lost(mine[0]);
       if (which == 0) {
         r->mom_it = 0;
         for (const KState& k : mine) r->mom_it = std::max(r->mom_it, k.it);
@@ -285,9 +290,6 @@ void solve_shared(const std::vector<Run*>& runs, int which, KMethod m, hipStream
       }
     }
   }
-  if (again.empty()) return;
-  // repeated by the Jacobi form (Run::poisson_cg)
-  for (Run* r : again) r->prepare_jacobi();
   solve_shared(again, which, m, s, rc, st, mem);
 }
 

@@ -1614,12 +1614,15 @@ void Run::export_values(int pattern, const void* dev, int vbytes, double* out) {
 
 // One CG solve of the Poisson set from the current start. A multigrid solve
 // that fails (a mesh its hierarchy does not suit, a tolerance out of reach) is
-// repeated from zero by the Jacobi form, whose status is then the result.
+// repeated from zero by the Jacobi form, whose status is then the result; the
+// iterations of both are counted.
 int Run::poisson_cg(std::vector<KState>& hs) {
   int rc = krylov_solve(stream, set_p, KMethod::PCG, prm.check_every, hs, pinned, timer);
   if (rc == IPCS_OK || !set_p.mg) return rc;
-  prepare_jacobi();
-  return krylov_solve(stream, set_p, KMethod::PCG, prm.check_every, hs, pinned, timer);
+  prepare_jacobi(hs[0]);
+  rc = krylov_solve(stream, set_p, KMethod::PCG, prm.check_every, hs, pinned, timer);
+  count_lost(hs[0]);
+  return rc;
 }
 
 // BiCGStab's path through a long momentum solve depends on the last bit of its
@@ -1632,10 +1635,20 @@ int Run::poisson_cg(std::vector<KState>& hs) {
 constexpr int kMgMomentum = 40;
 void Run::choose_poisson_cg() { set_p.mg = mgh && mom_it <= kMgMomentum; }
 
-// The next solve of the Poisson set is the Jacobi form's, from x = 0.
-void Run::prepare_jacobi() {
+// The next solve of the Poisson set is the Jacobi form's, from x = 0, after a
+// multigrid solve that ended in the state failed.
+void Run::prepare_jacobi(const KState& failed) {
   set_p.mg = false;
+  lost_it = failed.it;
+  lost_checks = failed.nchecks;
   HIP_OK(hipMemsetAsync(set_p.h_groups[0].v[0].x, 0, sizeof(double) * n1, stream));
+}
+
+// Adds the iterations of the multigrid solve that this one repeated, if any.
+void Run::count_lost(KState& k) {
+  k.it += lost_it;
+  k.nchecks += lost_checks;
+  lost_it = lost_checks = 0;
 }
 
 // Pressure Poisson solve (eq. (9), second line). FP64 form: one Jacobi-CG

@@ -247,6 +247,7 @@ struct Run {
   double* mg_part = nullptr;
   double* mg_val2 = nullptr;             // second values of the last product
   int mom_it = 0;              // this step's momentum iterations (most of any component)
+  int lost_it = 0, lost_checks = 0;   // of a multigrid solve that is being repeated
   MGroup* mgroup = nullptr;
   double* spart = nullptr;    // scratch partials for one-off reductions [8192*2]
   uint32_t* scnt = nullptr;
@@ -316,7 +317,8 @@ struct Run {
   void export_values(int pattern, const void* dev, int vbytes, double* out);
   int pressure_solve(std::vector<KState>& hs, ipcs_step_stats* st);
   int poisson_cg(std::vector<KState>& hs);
-  void prepare_jacobi();
+  void prepare_jacobi(const KState& failed);
+  void count_lost(KState& k);
   // the Poisson CG of this step: multigrid, or Jacobi after a long momentum solve
   void choose_poisson_cg();
 };

@@ -1,0 +1,44 @@
+"""A pressure solve that multigrid does not bring to the tolerance: the Jacobi
+form repeats it. A tolerance out of reach (1e-16) ends both, with the Jacobi
+form's status and the state of the last completed step."""
+import numpy as np
+import pytest
+
+from tests.gpu_common import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(I, torch, rows=0, prec=None, stream=None, n=60):
+    p = I.ipcs_params_default(nu=0.01, dt=1e-3, tol_p=1e-16, poisson_part_rows=rows,
+                              precision=I.IPCS_FP64 if prec is None else prec)
+    if prec == I.IPCS_MIXED:
+        p.tol_ir = 1e-16
+    r = I.Run(I.Mesh.unit_square(n), p, stream=stream)
+    r.set_builtin(I.IPCS_SOL_TAYLOR_GREEN_2D, (np.pi,))
+    return r
+
+
+def _failed(I, r):
+    with pytest.raises(I.IpcsError) as e:
+        r.advance(1)
+    assert e.value.stats[0].failed_solve == 2
+    return e.value.code, e.value.stats[0].it_p, e.value.stats[0].checks_p
+
+
+def test_the_iterations_of_both_forms_are_counted():
+    torch, I = require_gpu()
+    print("failed multigrid solve: iterations", flush=True)
+    named = _failed(I, _run(I, torch, rows=384))
+    both = _failed(I, _run(I, torch))
+    print(" ", named, both, flush=True)
+    assert both[0] == named[0] and both[1] > named[1] and both[2] >= named[2]
+    # a batch counts as a run alone does, in both precisions
+    for prec in (I.IPCS_FP64, I.IPCS_MIXED):
+        alone = _failed(I, _run(I, torch, prec=prec))
+        for step in (I.ipcs_batch_step, I.ipcs_batch_step_noalloc):
+            s = torch.cuda.Stream()
+            r = _run(I, torch, prec=prec, stream=s)
+            rc, st = step([r.h], s.cuda_stream)
+            print(" ", prec, alone, rc, st[0]["it_p"], st[0]["checks_p"], flush=True)
+            assert (rc, st[0]["it_p"], st[0]["checks_p"]) == alone

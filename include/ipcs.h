@@ -250,7 +250,8 @@ enum { IPCS_START_ZERO = 0, IPCS_START_PREVIOUS = 1 };
  * on the previous tentative velocities as well as on (U^n, P^n): a run resumed
  * through ipcs_set_state differs from the uninterrupted one within the
  * tolerance, not bit for bit. IPCS_MSTART_STATE: U^n at every step, a step
- * is a function of (U^n, P^n, t) alone. Dirichlet rows start at their data
+ * is a function of (U^n, P^n, t) alone (within the tolerance where a multigrid
+ * pressure solve has failed, poisson_part_rows below). Dirichlet rows start at their data
  * either way. */
 enum { IPCS_MSTART_EXTRAPOLATED = 0, IPCS_MSTART_STATE = 1 };
 
@@ -274,7 +275,8 @@ typedef struct {
                            * poisson_s 0) CG with a multigrid preconditioner
                            * above 2560 pressure rows after a momentum solve
                            * of at most 40 iterations, else (and where it
-                           * fails) Jacobi-CG in one kernel
+                           * fails, then and until a new state, viscosity,
+                           * time step or callback) Jacobi-CG in one kernel
                            * per iteration on a row partition of Kp into parts
                            * of at most 384 rows, falling back to two kernels
                            * where a part's halo does not fit in LDS; 64..2048

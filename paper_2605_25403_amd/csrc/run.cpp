@@ -1615,7 +1615,9 @@ void Run::export_values(int pattern, const void* dev, int vbytes, double* out) {
 // One CG solve of the Poisson set from the current start. A multigrid solve
 // that fails (a mesh its hierarchy does not suit, a tolerance out of reach) is
 // repeated from zero by the Jacobi form, whose status is then the result; the
-// iterations of both are counted.
+// iterations of both are counted. The following solves go to the Jacobi form at
+// once, until a new state or new parameters (clear_history): what made multigrid
+// fail, the mesh or the tolerance, is still there.
 int Run::poisson_cg(std::vector<KState>& hs) {
   int rc = krylov_solve(stream, set_p, KMethod::PCG, prm.check_every, hs, pinned, timer);
   if (rc == IPCS_OK || !set_p.mg) return rc;
@@ -1633,12 +1635,13 @@ int Run::poisson_cg(std::vector<KState>& hs) {
 // increment that it has always given, so that a run does not move by more than
 // its solves resolve when the preconditioner changes.
 constexpr int kMgMomentum = 40;
-void Run::choose_poisson_cg() { set_p.mg = mgh && mom_it <= kMgMomentum; }
+void Run::choose_poisson_cg() { set_p.mg = mgh && !mg_off && mom_it <= kMgMomentum; }
 
 // The next solve of the Poisson set is the Jacobi form's, from x = 0, after a
 // multigrid solve that ended in the state failed.
 void Run::prepare_jacobi(const KState& failed) {
   set_p.mg = false;
+  mg_off = true;
   lost_it = failed.it;
   lost_checks = failed.nchecks;
   HIP_OK(hipMemsetAsync(set_p.h_groups[0].v[0].x, 0, sizeof(double) * n1, stream));

@@ -247,6 +247,7 @@ struct Run {
   double* mg_part = nullptr;
   double* mg_val2 = nullptr;             // second values of the last product
   int mom_it = 0;              // this step's momentum iterations (most of any component)
+  bool mg_off = false;         // a multigrid solve failed: Jacobi until clear_history
   int lost_it = 0, lost_checks = 0;   // of a multigrid solve that is being repeated
   MGroup* mgroup = nullptr;
   double* spart = nullptr;    // scratch partials for one-off reductions [8192*2]
@@ -306,6 +307,7 @@ struct Run {
   // the next steps start their solves as the first after a new state would
   void clear_history() {
     mhist = 0;
+    mg_off = false;
     clear_pressure_start();
   }
   void correction_rhs();

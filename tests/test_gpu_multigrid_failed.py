@@ -42,3 +42,23 @@ def test_the_iterations_of_both_forms_are_counted():
             rc, st = step([r.h], s.cuda_stream)
             print(" ", prec, alone, rc, st[0]["it_p"], st[0]["checks_p"], flush=True)
             assert (rc, st[0]["it_p"], st[0]["checks_p"]) == alone
+
+
+def test_the_next_solves_go_to_the_jacobi_form_at_once():
+    torch, I = require_gpu()
+    print("failed multigrid solve: remembered", flush=True)
+    named = _failed(I, _run(I, torch, rows=384))
+    r = _run(I, torch)
+    U0 = r.velocity()
+    first, second = _failed(I, r), _failed(I, r)
+    r.set_builtin(I.IPCS_SOL_TAYLOR_GREEN_2D, (np.pi,))   # a new state tries again
+    third = _failed(I, r)
+    I.ipcs_set_time_step(r.h, 1e-3)                       # and so do new parameters
+    fourth = _failed(I, r)
+    print(" ", named, first, second, third, fourth, flush=True)
+    assert second == named and first == third == fourth and first[1] > second[1]
+    np.testing.assert_array_equal(r.velocity(), U0)
+    s = torch.cuda.Stream()
+    b = _run(I, torch, stream=s)
+    its = [I.ipcs_batch_step([b.h], s.cuda_stream)[1][0]["it_p"] for _ in range(2)]
+    assert its == [first[1], second[1]]

@@ -43,7 +43,15 @@ KERNELS = {
     "pcg_update_m": (8, "kernels_krylov.hip"),
     "pcg_fused_p": (9, "kernels_fcg.hip"),
     "asm_sum": (10, "kernels_asm.hip"),
+    "mg_product_p": (11, "kernels_mg.hpp"),
+    "mg_update_p": (12, "kernels_mg.hpp"),
+    "one_block_mom": (13, "kernels_small.hpp"),
+    "one_block_p": (14, "kernels_small.hpp"),
+    "one_block_corr": (15, "kernels_small.hpp"),
 }
+# without a byte model: the multigrid products differ from level to level, and a
+# whole solve in one block re-reads its matrix from registers or the L2
+NO_BYTES = ("mg_product_p", "one_block_mom", "one_block_p", "one_block_corr")
 
 
 def kernel_bytes(kernel, c, dim, vsz=8, p3=False):
@@ -57,6 +65,8 @@ def kernel_bytes(kernel, c, dim, vsz=8, p3=False):
     sl1, sl2 = 4 * (n1 // 64 + 2), 4 * (n2 // 64 + 2)     # SELL-64 slice pointers
     if kernel == "pcg_spmv_p":     # Kp values+cols once; u in, w = Kp u out
         return (vsz + 4) * nnz11 + sl1 + 2 * 8 * n1
+    if kernel == "mg_update_p":    # x, r, p, s, w, z in; x, r, p, s out
+        return 10 * 8 * n1
     if kernel == "pcg_update_p":   # x, r, p, s, w, dinv in; x, r, p, s, u out
         return 11 * 8 * n1
     if kernel == "bicg_spmv":      # A once for all components; phat, rhat in, v out each
@@ -927,15 +937,17 @@ def main():
         if kcnt[kid] == 0:
             continue
         us = 1000.0 * kms[kid] / kcnt[kid]
-        b = kernel_bytes(name, c, dim, 4 if mixed else 8, p3)
+        b = None if name in NO_BYTES else kernel_bytes(name, c, dim, 4 if mixed else 8, p3)
         if name == "pcg_fused_p":
             b *= ipl
-        kern[name] = {"us_per_launch": us, "bytes": b, "GBps": b / (us * 1e-6) / 1e9,
+        kern[name] = {"us_per_launch": us, "bytes": b,
+                      "GBps": b / (us * 1e-6) / 1e9 if b else None,
                       "launches_per_step": kcnt[kid] / ksteps,
                       "ms_per_step": kms[kid] / ksteps}
     roof = None
-    if kern:
-        dom = max(kern, key=lambda k: kern[k]["ms_per_step"])
+    modelled = [k for k in kern if kern[k]["bytes"]]
+    if modelled:
+        dom = max(modelled, key=lambda k: kern[k]["ms_per_step"])
         vb = 4 if mixed else 8
         ub = unit_bytes(dom, c, dim, vb)
         if ub is not None and dom == "pcg_fused_p":

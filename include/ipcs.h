@@ -468,7 +468,14 @@ enum {                            /* kernels of the step, for the timing hooks  
                                    * halo recomputation, w = Kp u; r.u, r.r, w.u    */
   IPCS_KERNEL_ASM_SUM = 10,       /* convection assembly, second pass (3D): the
                                    * cells' local rows added into the matrix rows   */
-  IPCS_NKERNEL = 11
+  IPCS_KERNEL_MG_PRODUCT_P = 11,  /* Poisson CG, multigrid: one sparse product of
+                                   * z = B r (on small meshes the last one forms
+                                   * w = Kp z too, else IPCS_KERNEL_PCG_SPMV_P does) */
+  IPCS_KERNEL_MG_UPDATE_P = 12,   /* Poisson CG, multigrid: p, s, x, r updates; r.r  */
+  IPCS_KERNEL_ONE_BLOCK_MOM = 13, /* a whole momentum solve in one block per component */
+  IPCS_KERNEL_ONE_BLOCK_P = 14,   /* a whole Poisson solve in one block              */
+  IPCS_KERNEL_ONE_BLOCK_CORR = 15,/* a whole correction solve in one block per component */
+  IPCS_NKERNEL = 16
 };
 /* Measurement hook (not part of the method): from the next call on, every
  * launch of a kernel whose bit (1 << IPCS_KERNEL_*) is set in mask is
@@ -476,10 +483,12 @@ enum {                            /* kernels of the step, for the timing hooks  
  * the step; mask = 0 turns this off. Accumulated times are reset. */
 int ipcs_kernel_timing(ipcs_run r, uint32_t mask);
 /* Accumulated event time (ms) and launch count per kernel since the last
- * ipcs_kernel_timing call; ms and launches hold cap >= IPCS_NKERNEL entries. */
+ * ipcs_kernel_timing call; ms and launches hold cap entries, of which the first
+ * IPCS_NKERNEL are written (IPCS_E_INVALID for fewer than 11, the kernels up to
+ * IPCS_KERNEL_ASM_SUM). */
 int ipcs_kernel_times(ipcs_run r, double* ms, int64_t* launches, int32_t cap);
 /* Measurement hook (not part of the method): launches one of the step's
- * kernels nlaunch times back to back on the run's stream with the run's own
+ * kernels (up to IPCS_KERNEL_ASM_SUM, else IPCS_E_INVALID) nlaunch times back to back on the run's stream with the run's own
  * data and returns the mean duration per launch in microseconds, timed with
  * HIP events on that stream. Leaves the run's Krylov scratch vectors
  * undefined (the next solve re-initializes them); the solver states

@@ -650,10 +650,10 @@ int ipcs_kernel_timing(ipcs_run r, uint32_t mask) {
 
 int ipcs_kernel_times(ipcs_run r, double* ms, int64_t* launches, int32_t cap) {
   return guard([&]() -> int {
-    need(ms != nullptr && launches != nullptr && cap >= IPCS_NKERNEL,
-         "need outputs with room for IPCS_NKERNEL entries");
+    need(ms != nullptr && launches != nullptr && cap > IPCS_KERNEL_ASM_SUM,
+         "need outputs with room for the kernels up to IPCS_KERNEL_ASM_SUM");
     const ipcs::KTimer& T = R(r).timer;
-    for (int k = 0; k < IPCS_NKERNEL; ++k) {
+    for (int k = 0; k < std::min<int>(cap, IPCS_NKERNEL); ++k) {
       ms[k] = T.ms[k];
       launches[k] = T.cnt[k];
     }

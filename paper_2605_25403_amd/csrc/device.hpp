@@ -356,7 +356,8 @@ void small_solve(hipStream_t s, const KLaunch& L, bool pcg, SmallForm f, int nma
 // group's finest input (FP64 values)
 void mg_cycle(hipStream_t s, const MGroup* groups, int nvec, const int* nblocks, double scale,
               const double* add, double* out, int64_t ld);
-void mg_apply(hipStream_t s, const KLaunch& L, const MLaunch& M, int par);   // stop test, z = B r, r.z
+// product slot of z = B r (M.nblocks[slot] > 0): the first with the stop test, the last with r.z
+void mg_product(hipStream_t s, const KLaunch& L, const MLaunch& M, int slot, int par);
 void mg_update(hipStream_t s, const KLaunch& L, const MLaunch& M, int par);  // p, s, x, r from z, w = A z
 
 // Fields and right-hand sides (kernels_fields.hip)

@@ -269,29 +269,27 @@ void mg_cycle(hipStream_t s, const MGroup* groups, int nvec, const int* nblocks,
 
 template <int KIND, class VT>
 static void mg_launch(hipStream_t s, const KLaunch& L, const MLaunch& M, int slot, int par) {
-  if (M.nblocks[slot] == 0) return;
   if (KIND == 2 && L.ngroups == 1 && M.one.st[slot].val2)
-    hipLaunchKernelGGL((k_mg1<3, VT>), dim3(M.nblocks[slot]), dim3(KBS), 0, s, M.kone, M.one,
-                       M.one.st[slot], par);
+    launch(k_mg1<3, VT>, dim3(M.nblocks[slot]), dim3(KBS), 0, s, M.kone, M.one, M.one.st[slot],
+           par);
   else if (L.ngroups == 1 && M.one.part_z)
-    hipLaunchKernelGGL((k_mg1<KIND, VT>), dim3(M.nblocks[slot]), dim3(KBS), 0, s, M.kone, M.one,
-                       M.one.st[slot], par);
+    launch(k_mg1<KIND, VT>, dim3(M.nblocks[slot]), dim3(KBS), 0, s, M.kone, M.one,
+           M.one.st[slot], par);
   else
-    hipLaunchKernelGGL((k_mg<KIND, VT>), dim3(M.nblocks[slot], L.ngroups), dim3(KBS), 0, s,
-                       L.groups, M.groups, slot, par);
-  HIP_LAUNCH_OK();
+    launch(k_mg<KIND, VT>, dim3(M.nblocks[slot], L.ngroups), dim3(KBS), 0, s, L.groups, M.groups,
+           slot, par);
 }
 
 template <class VT>
-static void mg_apply_t(hipStream_t s, const KLaunch& L, const MLaunch& M, int par) {
-  mg_launch<0, VT>(s, L, M, 0, par);
-  for (int slot = 1; slot + 1 < MG_SLOTS; ++slot) mg_launch<1, VT>(s, L, M, slot, par);
-  mg_launch<2, VT>(s, L, M, MG_SLOTS - 1, par);
+static void mg_product_t(hipStream_t s, const KLaunch& L, const MLaunch& M, int slot, int par) {
+  if (slot == 0) mg_launch<0, VT>(s, L, M, slot, par);
+  else if (slot + 1 < MG_SLOTS) mg_launch<1, VT>(s, L, M, slot, par);
+  else mg_launch<2, VT>(s, L, M, slot, par);
 }
 
-void mg_apply(hipStream_t s, const KLaunch& L, const MLaunch& M, int par) {
-  if (M.fp32) mg_apply_t<float>(s, L, M, par);
-  else mg_apply_t<double>(s, L, M, par);
+void mg_product(hipStream_t s, const KLaunch& L, const MLaunch& M, int slot, int par) {
+  if (M.fp32) mg_product_t<float>(s, L, M, slot, par);
+  else mg_product_t<double>(s, L, M, slot, par);
 }
 
 void mg_update(hipStream_t s, const KLaunch& L, const MLaunch& M, int par) {

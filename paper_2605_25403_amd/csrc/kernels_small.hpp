@@ -310,9 +310,8 @@ __global__ void __launch_bounds__(small_bs(W)) k_small(const KGroup* groups) {
 template <bool PCG, int R, int W, class VT>
 static void small_launch(hipStream_t s, const KLaunch& L, int nmax) {
   const size_t lds = sizeof(double) * (size_t)nmax * (PCG ? 1 : 3);
-  hipLaunchKernelGGL((k_small<PCG, R, W, VT>), dim3(L.ns, L.ngroups), dim3(small_bs(W)), lds, s,
-                     L.groups);
-  HIP_LAUNCH_OK();
+  launch(k_small<PCG, R, W, VT>, dim3(L.ns, L.ngroups), dim3(small_bs(W)), (uint32_t)lds, s,
+         L.groups);
 }
 
 template <int W, bool FP32, class F>

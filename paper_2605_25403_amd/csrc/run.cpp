@@ -298,9 +298,11 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
   int ipl = fused ? S.F.ipl : 1;   // iterations per launch
   auto iterate = [&](int par) {
     if (mg) {
-      mg_apply(s, S.L, S.M, par);
-      if (!S.M.with_w) pcg_spmv_only(s, S.L);
-      mg_update(s, S.L, S.M, par);
+      for (int slot = 0; slot < MG_SLOTS; ++slot)
+        if (S.M.nblocks[slot] > 0)
+          T.run(s, S.kid_mg[0], [&] { mg_product(s, S.L, S.M, slot, par); });
+      if (!S.M.with_w) T.run(s, S.kid_mg[1], [&] { pcg_spmv_only(s, S.L); });
+      T.run(s, S.kid_mg[2], [&] { mg_update(s, S.L, S.M, par); });
     } else if (fused) {
       T.run(s, S.kid[0], [&] { fcg_iter(s, S.F, par); });
     } else if (m == KMethod::PCG) {
@@ -330,7 +332,7 @@ int krylov_solve(hipStream_t s, KSet& S, KMethod m, int check_every, std::vector
   if (S.small.rows) {
     int nmax = 0;
     for (const KGroup& g : S.h_groups) nmax = std::max(nmax, (int)g.n);
-    small_solve(s, S.L, m == KMethod::PCG, S.small, nmax);
+    T.run(s, S.kid_small, [&] { small_solve(s, S.L, m == KMethod::PCG, S.small, nmax); });
     fetch();
     return result();
   }
@@ -1131,6 +1133,12 @@ void Run::setup_solvers() {
   for (int k = 0; k < 4; ++k) set_mom.kid[k] = kid_mom[k];
   set_p.kid[0] = pp ? IPCS_KERNEL_PCG_FUSED_P : IPCS_KERNEL_PCG_SPMV_P;
   set_p.kid[1] = pp ? -1 : IPCS_KERNEL_PCG_UPDATE_P;
+  set_p.kid_mg[0] = IPCS_KERNEL_MG_PRODUCT_P;
+  set_p.kid_mg[1] = IPCS_KERNEL_PCG_SPMV_P;
+  set_p.kid_mg[2] = IPCS_KERNEL_MG_UPDATE_P;
+  set_mom.kid_small = IPCS_KERNEL_ONE_BLOCK_MOM;
+  set_p.kid_small = IPCS_KERNEL_ONE_BLOCK_P;
+  set_corr.kid_small = IPCS_KERNEL_ONE_BLOCK_CORR;
   set_corr.kid[0] = IPCS_KERNEL_PCG_SPMV_M;
   set_corr.kid[1] = IPCS_KERNEL_PCG_UPDATE_M;
   HIP_OK(hipStreamSynchronize(stream));
@@ -1478,6 +1486,7 @@ int Run::step(ipcs_step_stats* st) {
 // data. The solver states are forced to "iterating" first and checked after:
 // every timed launch must have done its full work.
 double Run::profile_kernel(int kernel, int nlaunch) {
+  if (kernel < 0 || kernel > IPCS_KERNEL_ASM_SUM) fail(IPCS_E_INVALID, "unknown kernel id");
   if (phase_next != IPCS_PHASE_ASM) fail(IPCS_E_STATE, "profile only between steps");
   if (kernel < 0 || kernel >= IPCS_NKERNEL) fail(IPCS_E_INVALID, "unknown kernel id");
   const bool mom = kernel == IPCS_KERNEL_BICG_SPMV || kernel == IPCS_KERNEL_BICG_SPMV_T ||

@@ -95,6 +95,8 @@ struct KSet {
   // kernel ids for timing: PCG {spmv, update} (fused: {iteration}),
   // BiCGStab {v, s, t, x}; -1: none
   int kid[4] = {-1, -1, -1, -1};
+  int kid_mg[3] = {-1, -1, -1};   // multigrid: product, w = A z, update
+  int kid_small = -1;             // whole solves in one block
   // sets of several groups: device room for block maps over the groups that
   // are still unfinished (matrix, vector and fused maps back to back), so that
   // finished groups stop taking blocks; null: no compaction

@@ -50,7 +50,9 @@ IPCS_KERNEL_BICG_SPMV_T, IPCS_KERNEL_BICG_UPDATE_S, IPCS_KERNEL_BICG_UPDATE_X = 
 IPCS_KERNEL_PCG_UPDATE_M = 8
 IPCS_KERNEL_PCG_FUSED_P = 9
 IPCS_KERNEL_ASM_SUM = 10
-IPCS_NKERNEL = 11
+IPCS_KERNEL_MG_PRODUCT_P, IPCS_KERNEL_MG_UPDATE_P = 11, 12
+IPCS_KERNEL_ONE_BLOCK_MOM, IPCS_KERNEL_ONE_BLOCK_P, IPCS_KERNEL_ONE_BLOCK_CORR = 13, 14, 15
+IPCS_NKERNEL = 16
 
 
 class IpcsError(RuntimeError):

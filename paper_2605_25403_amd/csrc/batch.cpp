@@ -82,7 +82,10 @@ struct Plan {
 
 // Plans the shared sets for system set `which` (0 momentum, 1 Poisson,
 // 2 correction) of the given runs; returns the bytes their descriptors take.
-size_t plan_shared(const std::vector<Run*>& runs, int which, std::vector<Plan>& plans) {
+// Poisson sets: in the form of the solve at hand (NOW), or all in one form.
+enum class Form { NOW, JACOBI, MULTIGRID };
+size_t plan_shared(const std::vector<Run*>& runs, int which, std::vector<Plan>& plans,
+                   Form form = Form::NOW) {
   // one-block solves: (3 + width, ns, rows per thread, value type);
   // multigrid Poisson sets: (2, rows per thread, preconditioner's and matrix's
   // value types); fused Poisson sets: (1, iterations per launch, rows per
@@ -92,7 +95,8 @@ size_t plan_shared(const std::vector<Run*>& runs, int which, std::vector<Plan>& 
     const KSet& K = set_of(*r, which);
     if (K.small.rows)
       cls[{3 + K.small.width, K.L.ns, K.small.rows, K.L.fp32}].push_back(r);
-    else if (K.mg) cls[{2, K.L.ept_m, K.M.fp32, K.L.fp32}].push_back(r);
+    else if (form == Form::NOW ? K.mg : form == Form::MULTIGRID)
+      cls[{2, K.L.ept_m, K.M.fp32, K.L.fp32}].push_back(r);
     else if (K.fused) cls[{1, K.F.ipl, K.F.ept, K.F.fp32}].push_back(r);
     else cls[{0, K.L.ns, K.L.ept_m, K.L.fp32}].push_back(r);
   }
@@ -391,11 +395,20 @@ static void refine_shared(const std::vector<Run*>& runs, hipStream_t s, std::map
 size_t batch_descriptor_bytes(Run* const* runs, int nruns) {
   std::vector<Run*> all(runs, runs + nruns);
   std::vector<Plan> plans;
-  size_t most = 0;
   // a subset's descriptors (the plain or mixed Poisson runs, the runs still
   // refining) never take more room than the whole batch's
-  for (int which = 0; which < 3; ++which) most = std::max(most, plan_shared(all, which, plans));
-  return most;
+  size_t most = std::max(plan_shared(all, 0, plans), plan_shared(all, 2, plans));
+  // The step decides between multigrid and Jacobi run by run, and a multigrid
+  // solve that fails is repeated: room for every run in its Jacobi form, and
+  // beside it for what a run of a multigrid set has more (its table; at most
+  // five arrays of a set start on a 256-byte line).
+  size_t poisson = plan_shared(all, 1, plans, Form::JACOBI);
+  std::vector<Run*> mg;
+  for (Run* r : all)
+    if (r->mgh) mg.push_back(r);
+  plan_shared(mg, 1, plans, Form::MULTIGRID);
+  for (const Plan& p : plans) poisson += sizeof(MGroup) * p.rs.size() + 5 * 256;
+  return std::max(most, poisson);
 }
 
 int batch_step(Run* const* runs, int nruns, hipStream_t s, ipcs_step_stats* stats,

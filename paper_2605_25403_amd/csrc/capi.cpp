@@ -8,6 +8,8 @@
 #include <utility>
 #include <vector>
 
+#include <omp.h>
+
 #include "common.hpp"
 #include "ipcs.h"
 #include "mesh.hpp"
@@ -105,9 +107,9 @@ void vel_to_internal(const ipcs::Mesh& m, int ncomp, const double* in, double* o
   for (int c = 0; c < ncomp; ++c)
     for (int64_t i = 0; i < n; ++i) out[c * n + i] = in[c * n + m.v_out[i]];
 }
-// Brings n doubles to the host through a pinned buffer of two halves: while the
-// caller's threads move one half on (put(first, count, values), ranges of a
-// chunk in parallel), the next chunk is copied into the other.
+// Brings n doubles to the host through a pinned buffer of two halves: while up to
+// eight of the caller's OpenMP threads move one half on (put(first, count,
+// values), ranges of a chunk in parallel), the next chunk is copied into the other.
 template <class F>
 void read_back(hipStream_t s, const double* src, int64_t n, F put) {
   struct Lease {
@@ -137,7 +139,8 @@ void read_back(hipStream_t s, const double* src, int64_t n, F put) {
     const double* h = b.p + (c & 1) * H;
     constexpr int64_t kPiece = 16384;
     const int pieces = (int)((k + kPiece - 1) / kPiece);
-#pragma omp parallel for num_threads(std::min(pieces, 8)) schedule(static) if (pieces > 4)
+    const int team = std::min({pieces, 8, omp_get_max_threads()});
+#pragma omp parallel for num_threads(team) schedule(static) if (pieces > 4)
     for (int q = 0; q < pieces; ++q)
       put(a + q * kPiece, std::min(kPiece, k - q * kPiece), h + q * kPiece);
   }

@@ -114,14 +114,20 @@ template <class F>
 void read_back(hipStream_t s, const double* src, int64_t n, F put) {
   struct Lease {
     hipStream_t s;
-    double* p = ipcs::staging_take();
+    double* pinned = ipcs::staging_take();
+    std::unique_ptr<double[]> own;   // pageable, where no pinned buffer is free
+    double* p = pinned;
     bool sent = false;
-    explicit Lease(hipStream_t st) : s(st) {}
+    Lease(hipStream_t st, int64_t n) : s(st) {
+      if (p) return;
+      own.reset(new double[(size_t)std::min<int64_t>(n, 2 * ipcs::kStagingHalf)]);
+      p = own.get();
+    }
     ~Lease() {
       if (sent) (void)hipStreamSynchronize(s);   // no copy outlives the lease
-      ipcs::staging_give(p);
+      ipcs::staging_give(pinned);
     }
-  } b(s);
+  } b(s, n);
   constexpr int64_t H = ipcs::kStagingHalf;
   const int64_t chunks = (n + H - 1) / H;
   auto copy = [&](int64_t c) {

@@ -166,7 +166,9 @@ void pinned_give(KState* p) {
   g_pinned_free.push_back(p);
 }
 
-static std::vector<double*> g_staging_free;   // under g_pinned_mu
+// under g_pinned_mu
+static std::vector<double*> g_staging_free;
+static int g_staging_made = 0;
 
 double* staging_take() {
   {
@@ -176,22 +178,24 @@ double* staging_take() {
       g_staging_free.pop_back();
       return p;
     }
+    if (g_staging_made == kStagingKept) return nullptr;
+    g_staging_free.reserve(kStagingKept);
+    ++g_staging_made;
   }
   double* p = nullptr;
-  HIP_OK(hipHostMalloc((void**)&p, sizeof(double) * 2 * kStagingHalf, hipHostMallocDefault));
-  return p;
+  if (hipHostMalloc((void**)&p, sizeof(double) * 2 * kStagingHalf, hipHostMallocDefault) ==
+      hipSuccess)
+    return p;
+  (void)hipGetLastError();
+  std::lock_guard<std::mutex> lock(g_pinned_mu);
+  --g_staging_made;
+  return nullptr;
 }
 
 void staging_give(double* p) {
   if (!p) return;
-  {
-    std::lock_guard<std::mutex> lock(g_pinned_mu);
-    if ((int)g_staging_free.size() < kStagingKept) {
-      g_staging_free.push_back(p);
-      return;
-    }
-  }
-  (void)hipHostFree(p);
+  std::lock_guard<std::mutex> lock(g_pinned_mu);
+  g_staging_free.push_back(p);
 }
 
 LaunchEvents*& launch_events() {

@@ -130,7 +130,9 @@ void pinned_give(KState* p);
 // runtime a little at a time, and the renumbering was one thread's (64^3 cubes,
 // 53 MB: 17 to 20 ms; through these, by up to eight threads, 1.5 to 3 ms; 512^2
 // squares, 19 MB: 2.1 and 0.5 ms).
-// Taken for one call; at most kStagingKept stay with the process between calls.
+// Taken for one call. At most kStagingKept are made, and stay with the process:
+// freeing pinned memory waits for every stream of the device. Null where all are
+// out or the host has no pinned memory left; such a call goes without.
 constexpr int64_t kStagingHalf = 512 * 1024;
 constexpr int kStagingKept = 4;
 double* staging_take();

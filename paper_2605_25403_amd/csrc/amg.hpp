@@ -27,6 +27,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <exception>
 #include <memory>
 #include <vector>
 
@@ -55,12 +56,28 @@ inline int max_threads() {
 #endif
 }
 
+// Runs f(t) for t in [0, nt), one thread each. An exception (memory that runs out
+// inside f) may not leave a parallel region: the first one is thrown after it.
+template <class F>
+void team(int nt, F f) {
+  std::exception_ptr first;
+#pragma omp parallel for num_threads(nt) schedule(static, 1)
+  for (int t = 0; t < nt; ++t) {
+    try {
+      f(t);
+    } catch (...) {
+#pragma omp critical(ipcs_amg_team)
+      if (!first) first = std::current_exception();
+    }
+  }
+  if (first) std::rethrow_exception(first);
+}
+
 // Runs f(t, lo, hi) over contiguous ranges of [0, n), one per thread.
 template <class F>
 void ranges(int64_t n, F f) {
   const int nt = (int)std::min<int64_t>(max_threads(), std::max<int64_t>(1, n / 512));
-#pragma omp parallel for num_threads(nt) schedule(static, 1)
-  for (int t = 0; t < nt; ++t) f(t, n * t / nt, n * (t + 1) / nt);
+  team(nt, [&](int t) { f(t, n * t / nt, n * (t + 1) / nt); });
 }
 
 // Row pointers from the row lengths held in C.rp[1..], and room for the
@@ -144,11 +161,10 @@ inline Csr transpose(const Csr& A) {
   T.val.alloc(A.nnz());
   const int nt = (int)std::min<int64_t>(max_threads(), std::max<int64_t>(1, A.n / 4096));
   std::vector<std::vector<int32_t>> pos(nt);
-#pragma omp parallel for num_threads(nt) schedule(static, 1)
-  for (int t = 0; t < nt; ++t) {
+  team(nt, [&](int t) {
     pos[t].assign(T.n, 0);
     for (int32_t q = A.rp[A.n * t / nt]; q < A.rp[A.n * (t + 1) / nt]; ++q) pos[t][A.col[q]] += 1;
-  }
+  });
   int32_t at = 0;
   for (int64_t i = 0; i < T.n; ++i) {
     T.rp[i] = at;
@@ -159,14 +175,14 @@ inline Csr transpose(const Csr& A) {
     }
   }
   T.rp[T.n] = at;
-#pragma omp parallel for num_threads(nt) schedule(static, 1)
-  for (int t = 0; t < nt; ++t)
+  team(nt, [&](int t) {
     for (int64_t i = A.n * t / nt; i < A.n * (t + 1) / nt; ++i)
       for (int32_t q = A.rp[i]; q < A.rp[i + 1]; ++q) {
         const int32_t k = pos[t][A.col[q]]++;
         T.col[k] = (int32_t)i;
         T.val[k] = A.val[q];
       }
+  });
   return T;
 }
 

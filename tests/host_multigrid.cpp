@@ -1,9 +1,12 @@
 // Checks of the multigrid hierarchy (amg.hpp) on the CPU: every row of every
-// product in exactly one block of a bounded number of blocks.
+// product in exactly one block of a bounded number of blocks; memory that runs
+// out anywhere in its construction.
+#include <atomic>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <memory>
+#include <new>
 #include <vector>
 
 #include "amg.hpp"
@@ -19,6 +22,51 @@ using namespace ipcs;
       std::exit(2);                                                          \
     }                                                                        \
   } while (0)
+
+// The allocation that is to fail, counted down from where it is armed (< 0: none).
+static std::atomic<long> g_left{-1};
+static std::atomic<bool> g_armed{false};
+static void* counted(std::size_t n) {
+  if (g_armed && g_left.fetch_sub(1) == 0) throw std::bad_alloc();
+  if (void* p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void* operator new(std::size_t n) { return counted(n); }
+void* operator new[](std::size_t n) { return counted(n); }
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete[](void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
+void operator delete[](void* p, std::size_t) noexcept { std::free(p); }
+
+// Each allocation of a hierarchy fails in turn: the call throws, and the next
+// one builds it. (Enough rows for several threads.)
+static void out_of_memory() {
+  for (int pair : {0, 1})
+    for (bool velocity : {false, true}) {
+      if (velocity && pair == 1) continue;   // P2-P1 only
+      std::unique_ptr<Mesh> m(pair ? build_unit_square(20, 20, 1) : build_unit_square(36, 36));
+      long failed = 0;
+      for (long k = 0;; ++k) {
+        g_left = k;
+        g_armed = true;
+        bool threw = false;
+        std::shared_ptr<const MgHierarchy> h;
+        try {
+          h = velocity ? m->velocity_multigrid() : m->multigrid();
+        } catch (const std::bad_alloc&) {
+          threw = true;
+        }
+        g_armed = false;
+        if (!threw) {
+          CHECK(h != nullptr && g_left >= 0);
+          break;
+        }
+        ++failed;
+      }
+      std::printf("pair %d velocity %d: %ld allocations\n", pair, (int)velocity, failed);
+      CHECK(failed > 50);
+    }
+}
 
 static void check_jobs(const MgHierarchy& h) {
   for (int k = 0; k < MG_SLOTS; ++k) {
@@ -48,6 +96,7 @@ static void large_meshes() {
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "large")) large_meshes();
+  else if (!std::strcmp(what, "memory")) out_of_memory();
   else return 1;
   std::printf("ok\n");
 }

@@ -38,3 +38,8 @@ def run(exe, what):
 def test_the_last_product_fits_the_partial_sums_of_large_meshes(program):
     """1024^2 squares and 80^3 cubes are past 8192 blocks of the usual size."""
     run(program, "large")
+
+
+def test_memory_that_runs_out_is_an_exception(program):
+    """Also inside the parallel regions, where one that leaves ends the process."""
+    run(program, "memory")

@@ -718,7 +718,8 @@ inline Csr p1_to_velocity(const Mesh& m) {
 }
 
 // The hierarchy's products for the symmetric matrix A (constants in its null
-// space if singular), or null where aggregation does not coarsen it. P0 (may be null):
+// space if singular), or null where aggregation does not coarsen it or a product
+// has too many entries. P0 (may be null):
 // the prolongator of the finest level, taken over.
 inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0, bool singular) {
   std::vector<Level> lev;
@@ -767,7 +768,9 @@ inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0, bool singular) {
       for (int64_t i = 0; i < A.n; ++i) s[i] = -4.0 / 3.0 / lam * L.dinv[i];
       P = product(A, T, &T, s.data());
     }
+    if (P.n == 0) return nullptr;
     const Csr AP = product(A, P);
+    if (AP.n == 0) return nullptr;
     for (int64_t i = 0; i < A.n; ++i) s[i] = -L.omega * L.dinv[i];
     L.Q = smoothed(P, AP, s);
     if (sweeps == 2) {
@@ -776,7 +779,7 @@ inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0, bool singular) {
       L.Q = smoothed(L.Q, AQ, s);
     }
     Csr Ac = product(transpose(P), AP);
-    if (P.n == 0 || AP.n == 0 || L.Q.n == 0 || Ac.n == 0) return nullptr;
+    if (Ac.n == 0) return nullptr;
     L.A = std::move(A);
     lev.push_back(std::move(L));
     A = std::move(Ac);
@@ -798,11 +801,15 @@ inline std::shared_ptr<MgHierarchy> build(Csr A0, Csr* P0, bool singular) {
   std::vector<const Csr*> rows, diags, parts;
   std::vector<int32_t> zero, block, shift{0};
   const Csr lam = smoother(lev[base], sweeps);
+  if (lam.n == 0) return nullptr;
   parts.push_back(&lam);
   for (int k = base + 1; k < nl; ++k) {
     if (from(k).n == 0) return nullptr;
     Rt[k] = transpose(from(k));
-    if (k + 1 < nl) Sm[k] = smoother(lev[k], sweeps);
+    if (k + 1 < nl) {
+      Sm[k] = smoother(lev[k], sweeps);
+      if (Sm[k].n == 0) return nullptr;
+    }
     rows.push_back(&Rt[k]);
     diags.push_back(k + 1 < nl ? &Sm[k] : &B);
     parts.push_back(&from(k));

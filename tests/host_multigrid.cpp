@@ -1,6 +1,6 @@
 // Checks of the multigrid hierarchy (amg.hpp) on the CPU: every row of every
 // product in exactly one block of a bounded number of blocks; memory that runs
-// out anywhere in its construction.
+// out anywhere in its construction; products of too many entries.
 #include <atomic>
 #include <cstdio>
 #include <cstdlib>
@@ -68,6 +68,37 @@ static void out_of_memory() {
     }
 }
 
+// A product past 2^31 entries (4200 rows of 600000) has no hierarchy.
+static void too_many_entries() {
+  const int32_t n = 4200, m = 600000;
+  amg::Csr A, P;
+  A.n = A.m = P.n = n;
+  P.m = m;
+  A.rp.push_back(0);
+  P.rp.push_back(0);
+  for (int32_t i = 0; i < n; ++i) {
+    A.rp.push_back(A.rp.back() + (i + 1 < n ? 2 : 1));
+    P.rp.push_back(P.rp.back() + (i + 1 < n ? 1 : m));
+  }
+  A.col.alloc(A.nnz());
+  A.val.alloc(A.nnz());
+  P.col.alloc(P.nnz());
+  P.val.alloc(P.nnz());
+  for (int32_t i = 0; i < n; ++i) {
+    A.col[A.rp[i]] = i;
+    A.val[A.rp[i]] = 2.0;
+    if (i + 1 < n) {
+      A.col[A.rp[i] + 1] = n - 1;
+      A.val[A.rp[i] + 1] = -1.0 / n;
+    }
+  }
+  for (int32_t q = 0; q < P.nnz(); ++q) {
+    P.col[q] = q < n - 1 ? q : q - (n - 1);
+    P.val[q] = 1.0;
+  }
+  CHECK(amg::build(std::move(A), &P, true) == nullptr);
+}
+
 static void check_jobs(const MgHierarchy& h) {
   for (int k = 0; k < MG_SLOTS; ++k) {
     const MgProduct& p = h.st[k];
@@ -97,6 +128,7 @@ int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "large")) large_meshes();
   else if (!std::strcmp(what, "memory")) out_of_memory();
+  else if (!std::strcmp(what, "entries")) too_many_entries();
   else return 1;
   std::printf("ok\n");
 }

@@ -43,3 +43,8 @@ def test_the_last_product_fits_the_partial_sums_of_large_meshes(program):
 def test_memory_that_runs_out_is_an_exception(program):
     """Also inside the parallel regions, where one that leaves ends the process."""
     run(program, "memory")
+
+
+def test_too_many_entries_mean_no_hierarchy(program):
+    """A product past the 32-bit row pointers is not read as an operand."""
+    run(program, "entries")

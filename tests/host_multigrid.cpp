@@ -1,7 +1,9 @@
 // Checks of the multigrid hierarchy (amg.hpp) on the CPU: every row of every
-// product in exactly one block of a bounded number of blocks; memory that runs
-// out anywhere in its construction; products of too many entries.
+// product in exactly one block of a bounded number of blocks, a symmetric and
+// positive cycle; memory that runs out anywhere in its construction; products of
+// too many entries.
 #include <atomic>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -110,9 +112,147 @@ static void check_jobs(const MgHierarchy& h) {
     }
     for (int64_t r = 0; r < p.n; ++r) CHECK(seen[r] == 1);
   }
+  uint64_t bits = 1469598103934665603u;
+  auto hash = [&](const void* p, size_t n) {
+    for (size_t i = 0; i < n; ++i) bits = (bits ^ static_cast<const uint8_t*>(p)[i]) * 1099511628211u;
+  };
+  for (const MgProduct& p : h.st) {
+    hash(p.rp.data(), p.rp.size() * 4);
+    hash(p.col.data(), p.col.size() * 4);
+    hash(p.val.data(), p.val.size() * 8);
+    hash(p.val2.data(), p.val2.size() * 8);
+  }
   const size_t last = h.st[MG_SLOTS - 1].jobs.size();
-  std::printf("%lld rows: %zu blocks in the last product\n", (long long)h.n, last);
+  std::printf("%lld rows: %zu blocks in the last product, %016llx\n", (long long)h.n, last,
+              (unsigned long long)bits);
   CHECK(last >= 1 && last <= 8192);
+}
+
+static std::vector<double> times(const MgProduct& p, const RawVec<double>& val,
+                                 const std::vector<double>& x) {
+  std::vector<double> y(p.n, 0.0);
+  for (int64_t i = 0; i < p.n; ++i)
+    for (int32_t q = p.rp[i]; q < p.rp[i + 1]; ++q) {
+      CHECK(p.col[q] >= 0 && p.col[q] < (int64_t)x.size());
+      y[i] += val[q] * x[p.col[q]];
+    }
+  return y;
+}
+
+static std::vector<double> joined(std::vector<double> a, const std::vector<double>& b) {
+  a.insert(a.end(), b.begin(), b.end());
+  return a;
+}
+
+// z = B r by the products, as mesh.hpp states their inputs; the last one's input
+// is left in `in`.
+static std::vector<double> cycle(const MgHierarchy& h, const std::vector<double>& r,
+                                 std::vector<double>& in) {
+  auto mul = [&](int k, const std::vector<double>& x) { return times(h.st[k], h.st[k].val, x); };
+  if (h.base == 0) {
+    in = joined(r, mul(2, mul(0, r)));
+  } else {
+    const std::vector<double> r1 = mul(0, r);
+    CHECK((int64_t)r1.size() == h.nbase);
+    const std::vector<double> e = mul(2, mul(1, r1));
+    CHECK((int64_t)e.size() == h.below);
+    in = joined(r, mul(3, joined(r1, e)));
+  }
+  return mul(MG_SLOTS - 1, in);
+}
+
+static double dot(const std::vector<double>& a, const std::vector<double>& b) {
+  double s = 0.0;
+  for (size_t i = 0; i < a.size(); ++i) s += a[i] * b[i];
+  return s;
+}
+
+// The cycle is symmetric and positive (off the constants, where singular), and
+// second values give w = A z.
+static void check_cycle(const MgHierarchy& h, const amg::Csr& A, bool singular) {
+  CHECK(h.n == A.n);
+  std::vector<double> x(h.n), y(h.n), in;
+  uint32_t s = 12345;
+  double mx = 0.0, my = 0.0;
+  for (int64_t i = 0; i < h.n; ++i) {
+    x[i] = (s = s * 1664525u + 1013904223u) / 4294967296.0 - 0.5;
+    y[i] = (s = s * 1664525u + 1013904223u) / 4294967296.0 - 0.5;
+    mx += x[i] / h.n;
+    my += y[i] / h.n;
+  }
+  if (singular)
+    for (int64_t i = 0; i < h.n; ++i) {
+      x[i] -= mx;
+      y[i] -= my;
+    }
+  const std::vector<double> by = cycle(h, y, in), bx = cycle(h, x, in);
+  const double xx = dot(x, bx), yy = dot(y, by);
+  CHECK(xx > 0.0 && yy > 0.0);
+  CHECK(std::fabs(dot(x, by) - dot(y, bx)) <= 1e-12 * std::sqrt(xx * yy));
+  const MgProduct& last = h.st[MG_SLOTS - 1];
+  if (last.val2.size() == 0) return;
+  const std::vector<double> w = times(last, last.val2, in);
+  double err = 0.0, top = 0.0;
+  for (int64_t i = 0; i < A.n; ++i) {
+    double v = 0.0, a = 0.0;
+    for (int32_t q = A.rp[i]; q < A.rp[i + 1]; ++q) {
+      v += A.val[q] * bx[A.col[q]];
+      a += std::fabs(A.val[q] * bx[A.col[q]]);
+    }
+    err = std::max(err, std::fabs(v - w[i]));
+    top = std::max(top, a);
+  }
+  CHECK(err <= 1e-12 * top);
+}
+
+// Meshes of both dimensions and pairs, strips, vertices moved and relabelled.
+static Mesh* moved(int dim, int n, int pair) {
+  std::unique_ptr<Mesh> m(dim == 2 ? build_unit_square(n, n) : build_unit_cube(n, n, n));
+  std::vector<double> X(m->nv * dim);
+  std::vector<int32_t> at(m->nv), cells(m->nc * (dim + 1));
+  uint32_t s = 99;
+  for (int64_t v = 0; v < m->nv; ++v) at[v] = (int32_t)v;
+  for (int64_t v = m->nv - 1; v > 0; --v)
+    std::swap(at[v], at[(s = s * 1664525u + 1013904223u) % (uint32_t)(v + 1)]);
+  for (int64_t v = 0; v < m->nv; ++v)
+    for (int b = 0; b < dim; ++b)
+      X[(size_t)at[v] * dim + b] =
+          m->X[(size_t)v * dim + b] +
+          (m->bmask[v] ? 0.0 : 0.15 / n * ((s = s * 1664525u + 1013904223u) / 2147483648.0 - 1.0));
+  for (int64_t c = 0; c < m->nc; ++c)
+    for (int j = 0; j <= dim; ++j) cells[c * (dim + 1) + j] = at[m->c2dp[c * m->nloc1 + j]];
+  return build_from_arrays(dim, m->nv, X.data(), m->nc, cells.data(), pair);
+}
+
+static void shapes() {
+  std::vector<std::unique_ptr<Mesh>> ms;
+  for (int n : {1, 2, 3, 15, 40, 53}) ms.emplace_back(build_unit_square(n, n));
+  ms.emplace_back(build_unit_square(300, 3));
+  ms.emplace_back(build_unit_square(170, 170));      // more than the composed products take
+  for (int n : {1, 4, 11}) ms.emplace_back(build_unit_cube(n, n, n));
+  ms.emplace_back(build_unit_cube(2, 3, 40));
+  for (int n : {1, 9, 24}) ms.emplace_back(build_unit_square(n, n, 1));
+  for (int n : {1, 5}) ms.emplace_back(build_unit_cube(n, n, n, 1));
+  for (int pair : {0, 1}) {
+    ms.emplace_back(moved(2, 22, pair));
+    ms.emplace_back(moved(3, 6, pair));
+  }
+  int made = 0;
+  for (const auto& m : ms) {
+    if (auto h = m->multigrid()) {
+      check_jobs(*h);
+      check_cycle(*h, amg::stiffness(*m, amg::pressure_space(*m), nullptr), true);
+      ++made;
+    }
+    if (m->n1 > m->nv) continue;
+    if (auto h = m->velocity_multigrid()) {
+      check_jobs(*h);
+      check_cycle(*h, amg::stiffness(*m, amg::velocity_space(*m), m->bmask.data()), false);
+      ++made;
+    }
+  }
+  std::printf("%d hierarchies\n", made);
+  CHECK(made > 20);
 }
 
 static void large_meshes() {
@@ -126,7 +266,8 @@ static void large_meshes() {
 
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
-  if (!std::strcmp(what, "large")) large_meshes();
+  if (!std::strcmp(what, "shapes")) shapes();
+  else if (!std::strcmp(what, "large")) large_meshes();
   else if (!std::strcmp(what, "memory")) out_of_memory();
   else if (!std::strcmp(what, "entries")) too_many_entries();
   else return 1;

@@ -28,11 +28,12 @@ def program(tmp_path_factory):
     return build(str(tmp_path_factory.mktemp("mg") / "host_multigrid"), ["-O2"])
 
 
-def run(exe, what):
+def run(exe, what, threads="4"):
     r = subprocess.run([exe, what], capture_output=True, text=True, timeout=600,
-                       env=dict(os.environ, OMP_NUM_THREADS="4"))
+                       env=dict(os.environ, OMP_NUM_THREADS=threads))
     assert r.returncode == 0 and "ok" in r.stdout, (r.returncode, r.stdout[-2000:],
                                                     r.stderr[-4000:])
+    return r.stdout
 
 
 def test_the_last_product_fits_the_partial_sums_of_large_meshes(program):
@@ -48,3 +49,18 @@ def test_memory_that_runs_out_is_an_exception(program):
 def test_too_many_entries_mean_no_hierarchy(program):
     """A product past the 32-bit row pointers is not read as an operand."""
     run(program, "entries")
+
+
+def test_hierarchies_are_clean_under_sanitizers(tmp_path):
+    """Both hierarchies of meshes of every kind under AddressSanitizer and
+    UndefinedBehaviorSanitizer: indices in range, a symmetric positive cycle."""
+    exe = build(str(tmp_path / "sanitized"),
+                ["-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all"])
+    run(exe, "shapes")
+
+
+def test_the_hierarchy_does_not_depend_on_the_threads(program):
+    """Every bit of every product on one thread and on seven (the checks above
+    without sanitizers)."""
+    out = [run(program, "shapes", n) for n in ("1", "7")]
+    assert out[0] == out[1] and out[0].count("rows") > 20

@@ -320,6 +320,14 @@ void fcg_gather_values(hipStream_t s, bool fp32, int64_t nent, const int32_t* sr
 void fcg_gather_dinv(hipStream_t s, int64_t n, const int32_t* perm, const double* dinv,
                      double* out);
 
+// f(first, count) over n groups whose number is a launch's y dimension, which
+// takes up to 65536 blocks.
+constexpr int GRID_Y = 65536;
+template <class F>
+void over_groups(int n, F f) {
+  for (int g = 0; g < n; g += GRID_Y) f(g, n - g < GRID_Y ? n - g : GRID_Y);
+}
+
 // Multigrid-preconditioned CG (kernels_mg.hpp) over the groups of a KLaunch
 // (one system each); groups[i] belongs to the KLaunch's group i. nblocks[s]:
 // the most blocks any group has in product s (0 skips it); a launch takes that

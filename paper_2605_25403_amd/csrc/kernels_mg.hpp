@@ -276,8 +276,10 @@ static void mg_launch(hipStream_t s, const KLaunch& L, const MLaunch& M, int slo
     launch(k_mg1<KIND, VT>, dim3(M.nblocks[slot]), dim3(KBS), 0, s, M.kone, M.one,
            M.one.st[slot], par);
   else
-    launch(k_mg<KIND, VT>, dim3(M.nblocks[slot], L.ngroups), dim3(KBS), 0, s, L.groups, M.groups,
-           slot, par);
+    over_groups(L.ngroups, [&](int g, int n) {
+      launch(k_mg<KIND, VT>, dim3(M.nblocks[slot], n), dim3(KBS), 0, s, L.groups + g,
+             M.groups + g, slot, par);
+    });
 }
 
 template <class VT>

@@ -310,8 +310,10 @@ __global__ void __launch_bounds__(small_bs(W)) k_small(const KGroup* groups) {
 template <bool PCG, int R, int W, class VT>
 static void small_launch(hipStream_t s, const KLaunch& L, int nmax) {
   const size_t lds = sizeof(double) * (size_t)nmax * (PCG ? 1 : 3);
-  launch(k_small<PCG, R, W, VT>, dim3(L.ns, L.ngroups), dim3(small_bs(W)), (uint32_t)lds, s,
-         L.groups);
+  over_groups(L.ngroups, [&](int g, int n) {
+    launch(k_small<PCG, R, W, VT>, dim3(L.ns, n), dim3(small_bs(W)), (uint32_t)lds, s,
+           L.groups + g);
+  });
 }
 
 template <int W, bool FP32, class F>

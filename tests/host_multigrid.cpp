@@ -13,6 +13,7 @@
 
 #include "amg.hpp"
 #include "common.hpp"
+#include "device.hpp"
 #include "mesh.hpp"
 
 using namespace ipcs;
@@ -264,10 +265,24 @@ static void large_meshes() {
   }
 }
 
+// Launches over more runs than the y dimension takes are cut up.
+static void launch_groups() {
+  for (int n : {1, 65535, 65536, 65537, 200000}) {
+    int at = 0, launches = 0;
+    over_groups(n, [&](int first, int count) {
+      CHECK(first == at && count >= 1 && count <= 65536);
+      at += count;
+      ++launches;
+    });
+    CHECK(at == n && launches == (n + 65535) / 65536);
+  }
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "shapes")) shapes();
   else if (!std::strcmp(what, "large")) large_meshes();
+  else if (!std::strcmp(what, "groups")) launch_groups();
   else if (!std::strcmp(what, "memory")) out_of_memory();
   else if (!std::strcmp(what, "entries")) too_many_entries();
   else return 1;

@@ -64,3 +64,8 @@ def test_the_hierarchy_does_not_depend_on_the_threads(program):
     without sanitizers)."""
     out = [run(program, "shapes", n) for n in ("1", "7")]
     assert out[0] == out[1] and out[0].count("rows") > 20
+
+
+def test_launches_over_many_runs_keep_to_the_grid(program):
+    """The shared launches of a batch take a run per y block, at most 65536."""
+    run(program, "groups")

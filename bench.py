@@ -579,6 +579,7 @@ def pair_forms(w, steps, torch, I, dim=2, n=None):
                      "pressure_dofs": int(c.n1), "value": ndof / (ms / 1000.0),
                      "p50_step_ms": ms, "pressure_iterations_median": float(np.median(it_p)),
                      "asm_conv_us": asm,
+                     "mg_product_p_us": us(I.IPCS_KERNEL_MG_PRODUCT_P),
                      "pcg_fused_p_us": fus, "pcg_fused_p_GBps": fgb,
                      "pcg_fused_p_frac_of_hbm_peak": fgb / PEAK_HBM_GBS if fgb else None,
                      "rel_l2_to_exact_u": eu, "rel_l2_to_exact_p": ep}

@@ -272,11 +272,17 @@ typedef struct {
                          * iteration costs more than a poll)                */
   int32_t callbacks;    /* 1: reserve staging for host-callback forcing        */
   int32_t poisson_part_rows; /* pressure Poisson CG form: 0 (default, with
-                           * poisson_s 0) CG with a multigrid preconditioner
-                           * above 2560 pressure rows after a momentum solve
-                           * of at most 40 iterations, else (and where it
-                           * fails, then and until a new state, viscosity,
-                           * time step or callback) Jacobi-CG in one kernel
+                           * poisson_s 0) Jacobi-CG whole in one block where Kp
+                           * fits its registers (up to 2048 rows of at most 8
+                           * entries, 1536 of at most 20); above, CG with a
+                           * multigrid preconditioner from 2561 pressure rows
+                           * on, or from 501 where some row has more than 8
+                           * entries (cubes, the P3-P2 pair, most unstructured
+                           * meshes), after a momentum solve of at most 40
+                           * iterations; below that size one block again, up to
+                           * 50000 entries; else (and where multigrid fails, then
+                           * and until a new state, viscosity, time step or
+                           * callback) Jacobi-CG in one kernel
                            * per iteration on a row partition of Kp into parts
                            * of at most 384 rows, falling back to two kernels
                            * where a part's halo does not fit in LDS; 64..2048
@@ -496,9 +502,11 @@ int ipcs_kernel_times(ipcs_run r, double* ms, int64_t* launches, int32_t cap);
  * as before. Call between steps only. */
 int ipcs_profile_kernel(ipcs_run r, int32_t kernel, int32_t nlaunch, double* us_per_launch);
 
-/* The pressure Poisson CG form the run uses for Kp dP = r (eq. (9), second
- * line; measurement and inspection). *rows_max receives the part size
- * of its row partition (0: two kernels per iteration, no partition), *nparts
+/* The row partition of the run's Jacobi-CG for Kp dP = r (eq. (9), second
+ * line; measurement and inspection), also where its solves take the multigrid
+ * or the one-block form (poisson_part_rows; ipcs_kernel_times shows which
+ * kernels ran). *rows_max receives the part size
+ * of the partition (0: two kernels per iteration, no partition), *nparts
  * the number of parts, *halo_rows the summed halo sizes (the rows a part reads
  * from other parts, once per part), *lds_rows the largest own + halo count of
  * a part. Any output pointer may be NULL. */
@@ -519,8 +527,9 @@ void ipcs_run_destroy(ipcs_run r);
  * eliminated (the iterates carry the Dirichlet data), by flexible GMRES with
  * the block upper-triangular preconditioner [[A, G], [0, -Mp / nu]]: A, the
  * velocity block, applied by two multigrid sweeps on nu K, Mp by Chebyshev
- * steps (no inner iterations); where its cycles gain too little (convection
- * dominates, or a short restart), from zero again with [[A, G],
+ * steps (no inner iterations); where a cycle gains less than a factor 30 (convection
+ * dominates, or a short restart) or the true residual stalls above the
+ * tolerance, from zero again with [[A, G],
  * [0, -(1/nu) diag(Mp 1)]], A applied by a loose inner Jacobi-BiCGStab solve.
  * lin_maxit bounds each of the two. The pressure is fixed by zero integral
  * mean after each step. The start is the Dirichlet data on the boundary and

@@ -194,8 +194,11 @@ inline std::vector<double> diagonal(const Csr& A) {
   return d;
 }
 
-// Largest eigenvalue of D^{-1} A from above: power iteration from a fixed
-// rough start, times a margin. The norms are summed chunk by chunk, so the
+// Estimate of the largest eigenvalue of D^{-1} A: 16 power iterations from a fixed
+// rough start, times 1.06. On squares, strips, cubes and boxes of both spaces it
+// lies between 0.97 and 1.03 of the eigenvalue; the weights 1.62 and 4/3 over the
+// estimate stay below 2 over the eigenvalue, as the smoothing steps need, down to
+// estimates of 0.81 of it. The norms are summed chunk by chunk, so the
 // result, and with it every bit of the hierarchy, is the same whatever the
 // number of threads.
 inline double lambda_max(const Csr& A, const std::vector<double>& dinv) {

@@ -627,9 +627,9 @@ void Run::choose_poisson_form() {
 // (4,225 rows) 1.42 / 0.55 ms, 512^2 17.3 / 1.3 ms (1,600 / 20 iterations), 64^3
 // 8.0 / 1.9 ms, P3-P2 on 256^2 27.1 / 1.4 ms; of the wide ones, 12^3 (2,197
 // rows) 1.0 / 0.51 ms, P3-P2 on 21^2 (1,849) 1.39 / 0.51 and on 4^3 (729) 1.05 /
-// 0.56 ms, where fewer rows take fewer than 70 Jacobi iterations. Between one
-// block's 2,048 short rows and kMgRows the one-launch-per-iteration form stays,
-// at most 170 iterations, whose counts its two-kernel twin reproduces.
+// 0.56 ms, where fewer rows take fewer than 70 Jacobi iterations. Between 2,048
+// short rows and kMgRows one block streams its matrix (at most 50,000 entries;
+// 45^2 to 49^2 squares 0.82 to 0.93 ms for 0.94 to 0.98 of a launch per iteration).
 constexpr int64_t kMgRows = 2560, kMgWide = 500;
 static_assert(MG_LAST_JOBS == KNB_MAX, "partial sums of a multigrid product");
 void Run::choose_preconditioner() {
@@ -1644,9 +1644,12 @@ int Run::poisson_cg(std::vector<KState>& hs) {
 // input: from about 45 iterations on, pressures that differ by 1e-15 lead to
 // tentative velocities that differ by all that the tolerance leaves open, and
 // to 1e-9 of the pressure a step later (at 40 and fewer: 1e-13).
-// After such a solve the pressure stays with the Jacobi form, bit for bit the
-// increment that it has always given, so that a run does not move by more than
-// its solves resolve when the preconditioner changes.
+// After such a solve the pressure stays with the Jacobi form, so that a run's
+// fields agree with those of the form named by poisson_part_rows to 1e-9. It is
+// no condition of the solve itself: both forms end at the same confirmed
+// residual. Its price is the step time past the line: at 512^2 1,500 to 1,900
+// Jacobi iterations, 16 to 27 ms, where multigrid takes 1.2 to 1.4 ms. A momentum
+// solve that stays short at every viscosity would do without it.
 constexpr int kMgMomentum = 40;
 void Run::choose_poisson_cg() { set_p.mg = mgh && !mg_off && mom_it <= kMgMomentum; }
 
@@ -1671,7 +1674,8 @@ void Run::count_lost(KState& k) {
 // solve of Kp dP = r to tol_p. Mixed form: iterative refinement in FP64 on
 // the FP64 Kp: res = r - Kp dP (projected to zero sum), stop when
 // ||res|| <= tol_ir ||r||, else solve Kp32 d = res with Jacobi-CG on the FP32
-// matrix (FP64 vectors and sums) to a loose relative tolerance and add d.
+// matrix (FP64 vectors and sums; multigrid CG: on the FP64 one) to a loose
+// relative tolerance and add d.
 int Run::pressure_solve(std::vector<KState>& hs, ipcs_step_stats* st) {
   if (!mixed) {
     const int rc = poisson_cg(hs);

@@ -17,9 +17,10 @@
 // whatever the mesh where viscosity dominates: 48^2 squares at nu = 1 took 303
 // iterations with 11898 inner ones in 387 ms, and take 188 in 22 ms (115 us an
 // iteration, the chain of launches); 8^3 cubes 639 and 142 ms. Where an FGMRES
-// cycle gains less than a factor 30 (20^2 squares at nu = 0.02: 870 ms before,
-// 770 ms now with the cycle tried first; nu = 0.005: 6130 and 6120 ms), the Newton system is solved again with A by a
-// loose inner Jacobi-BiCGStab solve and S = (1/nu) diag(Mp 1). The pressure is
+// cycle gains less than a factor 30 (20^2 squares at nu = 0.02: 870 ms without
+// the cycle, 720 ms with it tried first; nu = 0.005: 6130 and 6120 ms), the Newton
+// system is solved again with A by a loose inner Jacobi-BiCGStab solve and
+// S = (1/nu) diag(Mp 1). The pressure is
 // shifted to zero integral mean after every step.
 #pragma once
 #include <hip/hip_runtime.h>

@@ -21,7 +21,7 @@ LaunchEvents*& launch_events();
 
 template <class... KArgs, class... Args>
 inline void launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, uint32_t shmem,
-                   hipStream_t s, Args... args) {
+                   hipStream_t s, const Args&... args) {
   LaunchEvents*& le = launch_events();
   if (le) {
     const LaunchEvents e = *le;

@@ -1658,6 +1658,7 @@ void Run::choose_poisson_cg() { set_p.mg = mgh && !mg_off && mom_it <= kMgMoment
 void Run::prepare_jacobi(const KState& failed) {
   set_p.mg = false;
   mg_off = true;
+  set_p.pace[1].last_iters = kMgIters;   // a failed solve's length is no guide
   lost_it = failed.it;
   lost_checks = failed.nchecks;
   HIP_OK(hipMemsetAsync(set_p.h_groups[0].v[0].x, 0, sizeof(double) * n1, stream));

@@ -62,3 +62,24 @@ def test_the_next_solves_go_to_the_jacobi_form_at_once():
     b = _run(I, torch, stream=s)
     its = [I.ipcs_batch_step([b.h], s.cuda_stream)[1][0]["it_p"] for _ in range(2)]
     assert its == [first[1], second[1]]
+
+
+def test_a_failed_solve_is_no_guide_for_the_next_ones_length():
+    """A solve of known length launches that many iterations before it looks at
+    the status. After a failed solve (more than the 18 iterations of a first one)
+    and a new state, a solve that is done at its start (everything is zero)
+    launches 19."""
+    torch, I = require_gpu()
+    print("failed multigrid solve: length", flush=True)
+    r = I.Run(I.Mesh.unit_square(60), I.ipcs_params_default(nu=0.01, dt=1e-3, tol_p=1e-16))
+    x = np.random.default_rng(1).standard_normal((2, r.n2))
+    r.set_state(x, np.zeros(r.n1), 0.0)
+    r.kernel_timing(1 << I.IPCS_KERNEL_MG_UPDATE_P)
+    _failed(I, r)
+    first = r.kernel_times()[1][I.IPCS_KERNEL_MG_UPDATE_P]
+    r.set_state(0 * x, np.zeros(r.n1), 0.0)
+    r.kernel_timing(1 << I.IPCS_KERNEL_MG_UPDATE_P)
+    st = r.advance(1)[0]
+    print(" ", first, r.kernel_times()[1][I.IPCS_KERNEL_MG_UPDATE_P], st, flush=True)
+    assert st["it_p"] == 0 and first > 19
+    assert r.kernel_times()[1][I.IPCS_KERNEL_MG_UPDATE_P] == 19

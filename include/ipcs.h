@@ -266,7 +266,8 @@ typedef struct {
   double tol_p;         /* pressure Poisson PCG (mixed: inner, see above)      */
   double tol_corr;      /* velocity-correction PCG                             */
   double tol_ir;        /* mixed form: FP64 iterative-refinement tolerance     */
-  int32_t maxit;        /* iteration cap per solve                             */
+  int32_t maxit;        /* iteration cap per solve (above 100000 no solve is one
+                         * launch, poisson_part_rows below)                   */
   int32_t check_every;  /* most iterations a solve launches between two status
                          * polls near its expected end (fewer when one
                          * iteration costs more than a poll)                */

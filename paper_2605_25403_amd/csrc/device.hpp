@@ -358,6 +358,10 @@ constexpr int small_rmax(int width, bool fp32) {
 // Most SELL entries of a streamed matrix: one CU reads about 150 GB/s, and at
 // this size its iteration costs what the four-kernel one does.
 constexpr int64_t SMALL_STREAM = 50000;
+// Largest iteration cap of a one-block solve: the host cannot end it, and at 2 to
+// 15 us an iteration this many hold the device for 0.2 to 1.5 s. With a larger
+// cap (the default is 20000) a run takes the forms that the host polls.
+constexpr int SMALL_MAXIT = 100000;
 SmallForm small_form(int64_t n, int maxw, int64_t nent, bool pcg, bool fp32);
 void small_solve(hipStream_t s, const KLaunch& L, bool pcg, SmallForm f, int nmax);
 // out (nvec vectors at stride ld) = scale B r (+ add), r at the head of each

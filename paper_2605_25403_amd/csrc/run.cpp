@@ -1069,7 +1069,8 @@ void Run::setup_solvers() {
     S.d_poll = poll + gi * GMAX;
     // small systems whole in one block, unless the parameters name a Poisson form
     const Sell& A = gi == 1 ? mesh->e11 : mesh->e22;
-    if (gi != 1 || (prm.poisson_part_rows == 0 && prm.poisson_s == 0 && !mgh))
+    if (prm.maxit <= SMALL_MAXIT &&
+        (gi != 1 || (prm.poisson_part_rows == 0 && prm.poisson_s == 0 && !mgh)))
       S.small = small_form(grp[gi].n, A.maxw, A.nent, gi != 0, mixed && gi != 1);
   };
   mk(set_mom, 0);

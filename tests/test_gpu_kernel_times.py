@@ -73,3 +73,25 @@ def test_kernels_without_a_launcher_of_their_own_and_shorter_outputs():
     assert I.lib.ipcs_kernel_times(r.h, ms, cnt, 11) == I.IPCS_OK      # as many as there were
     assert ms[10] == 0.0 and ms[11] == -1.0 and cnt[11] == -1
     assert I.lib.ipcs_kernel_times(r.h, ms, cnt, 10) == I.IPCS_E_INVALID
+
+
+@pytest.mark.parametrize("maxit,one_block", [(100000, True), (100001, False)])
+def test_no_single_launch_without_a_bound(maxit, one_block):
+    """A one-block solve cannot be ended by the host: past an iteration cap of
+    100000 small systems take the polled forms, to the same fields (1e-9: both
+    meet the default tolerance of 1e-12)."""
+    torch, I = require_gpu()
+    print(f"kernel times: maxit {maxit}", flush=True)
+    m, out = I.Mesh.unit_square(16), []
+    for cap in (20000, maxit):
+        r = I.Run(m, I.ipcs_params_default(nu=0.01, dt=1e-3, maxit=cap))
+        r.set_builtin(I.IPCS_SOL_TAYLOR_GREEN_2D, (np.pi,))
+        r.kernel_timing((1 << I.IPCS_NKERNEL) - 1)
+        r.advance(STEPS)
+        cnt = r.kernel_times()[1]
+        out.append((r.velocity(), r.pressure()))
+    print(" ", cnt, flush=True)
+    for k in (I.IPCS_KERNEL_ONE_BLOCK_MOM, I.IPCS_KERNEL_ONE_BLOCK_P, I.IPCS_KERNEL_ONE_BLOCK_CORR):
+        assert cnt[k] == (STEPS if one_block else 0)
+    for a, b in zip(*out):
+        assert np.linalg.norm(a - b) <= 1e-9 * np.linalg.norm(a)
